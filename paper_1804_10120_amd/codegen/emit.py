@@ -18,6 +18,8 @@ non-temporal accesses and XCD order as the hand-written kernels.
 """
 from __future__ import annotations
 
+import textwrap
+
 from .dsl import Bin, CodegenError, Const, Neg, Program, Ref, SumExpr
 
 
@@ -127,6 +129,7 @@ class _Emitter:
         self.pending = []        # loads referenced since the last statement was emitted
         self.written = set()     # (field, comp) of outputs with a value
         self.temp_written = set()  # (temporary, comp) with a value
+        self.stores = []           # (field, comp) of the stores, in program order
         self.lazy = sum(t.ncomp for t in self.ins) > LAZY_INPUTS
 
     def ref(self, e: Ref, env) -> str:
@@ -190,7 +193,8 @@ class _Emitter:
                 declared.add((f, c))
                 self.written.add((f, c))
                 stmts.append(f"    {decl}{var} = {rhs};")
-                stmts.append(f"    st({f}, {c}, {var});")
+                stmts.append(f"    st({len(self.stores)}, {f}, {c}, {var});")
+                self.stores.append((f, c))
 
     def body(self) -> str:
         lines = []
@@ -226,6 +230,14 @@ class _Emitter:
                  for (f, c), v in sorted(self.loaded.items())]
         return "\n".join(lines + loads + stmts)
 
+    def _store_table(self, name, part) -> str:
+        """constexpr function: the field (part 0) or component (part 1) of the k-th store."""
+        values = textwrap.fill(", ".join(str(st[part]) for st in self.stores), 92,
+                               initial_indent="        ", subsequent_indent="        ")
+        return (f"  static constexpr int {name}(int k) {{\n"
+                f"    constexpr unsigned char v[] = {{\n{values}}};\n"
+                f"    return v[k];\n  }}")
+
     def struct(self) -> str:
         p = self.p
         body = self.body()
@@ -241,6 +253,9 @@ struct Gen_{p.name} {{
   static constexpr int fin[NF_IN] = {{{fin}}};
   static constexpr int fout[NF_OUT] = {{{fout}}};
   static constexpr int NIN = {sum(t.ncomp for t in self.ins)}, NOUT = {sum(t.ncomp for t in self.outs)};
+  static constexpr int NST = {len(self.stores)};
+{self._store_table("store_f", 0)}
+{self._store_table("store_c", 1)}
   template <class L, class S>
   __device__ static inline void stream(L&& ld, S&& st) {{
 {body}

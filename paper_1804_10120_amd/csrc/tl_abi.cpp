@@ -46,11 +46,18 @@ struct Span {
   int ncomp;
 };
 
+// What the launch rules look at beside the kernel and n.
+struct Layout {
+  bool vec_ok = true;   // every field 16-byte aligned with even ld (for ppt = 2)
+  bool buf_ok = true;   // every field spans less than 4 GiB (32-bit buffer offsets)
+  bool line_ok = true;  // every output component starts on a 128-byte line
+  int64_t in_bytes = 0, out_bytes = 0;
+};
+
 struct Checker {
   int64_t n;
   std::vector<Span> spans;
-  bool vec_ok = true;  // every field 16-byte aligned with even ld (for ppt = 2)
-  bool buf_ok = true;  // every field spans less than 4 GiB (32-bit buffer offsets)
+  Layout lay;
   tl_status st = TL_OK;
 
   explicit Checker(int64_t n_) : n(n_) {}
@@ -77,9 +84,11 @@ struct Checker {
       st = fail(TL_ERR_ALIGN, "%s is not 8-byte aligned", name);
       return;
     }
-    if (a % 16 != 0 || (ncomp > 1 && ld % 2 != 0)) vec_ok = false;
+    if (a % 16 != 0 || (ncomp > 1 && ld % 2 != 0)) lay.vec_ok = false;
     const uintptr_t bytes = static_cast<uintptr_t>((ncomp - 1) * ld + n) * 8u;
-    if (bytes > 0xFFFFFFFFull) buf_ok = false;
+    if (bytes > 0xFFFFFFFFull) lay.buf_ok = false;
+    if (output && (a % 128 != 0 || (ncomp > 1 && ld % 16 != 0))) lay.line_ok = false;
+    (output ? lay.out_bytes : lay.in_bytes) += ncomp * n * 8;
     spans.push_back({name, a, a + bytes, output, static_cast<uintptr_t>(n) * 8u,
                      static_cast<uintptr_t>(ld) * 8u, ncomp});
   }
@@ -202,10 +211,46 @@ tl::Resolved defaults(tl::KernelId k, int64_t n) {
   return r;
 }
 
-tl_status resolve(tl::KernelId k, const tl_tune* t, bool vec_ok, bool buf_ok, int64_t n,
+// The kernel of a call that gives no launch shape: the staged one
+// (tl_stream.hpp, with what it measured) where it is the faster.
+//  - From 2^19 points: with whole lines the two kernels are within 1 % at 80^3
+//    and 97^3 points, and the staged one takes 2-5 % less from 2^21.  It then
+//    runs two blocks per compute unit (24 KB of LDS reserved beside its 32).
+//  - From 2^16 points if an output component does not start on a line: 45^3
+//    points are a draw, at 61^3 the adjoint takes 26.2 us against 29.7 us.
+//    Blocks are not held down below 2^19, where they would not fill the chip.
+//    The same for a batch, whose subgrids are ragged as a rule: 195 k points in
+//    48 aligned subgrids are a draw.
+// Tile order: runs of 4 tiles per XCD where tiles share lines (at 159^3 points
+// the adjoint takes 549, 534, 534 and 528 us in plain order and in runs of 4,
+// 8 and 16, Gamma 241, 240, 243 and 241 us); one range per XCD at exactly 2^20
+// and 2^21 points, as for defaults() above; else plain order, which at 160^3
+// beats runs of 4 by 1-4 %.
+// Loads stay in the L2 where the lines are shared and the body writes at least
+// half of what it reads: the adjoint over 159^3 points takes 504 us with them,
+// 534 without; Gamma 243 and 240, the forward 290 and 285 us (which reads seven
+// times what it writes, and keeps streaming).
+void default_path(tl::KernelId k, const Layout& lay, int64_t n, tl::Resolved* r) {
+  const bool batched = k == tl::KernelId::ChainBatched || k == tl::KernelId::ChainBwdBatched;
+  const int64_t few = int64_t(1) << 16, many = int64_t(1) << 19;
+  if (!lay.buf_ok || n < few || (n < many && lay.line_ok && !batched)) return;
+  r->path = tl::Path::Staged;
+  r->block = tl::kStageBlock;
+  r->ppt = 1;
+  r->lds_pad = n >= many ? 24 << 10 : 0;
+  r->keep_in = !lay.line_ok && 2 * lay.out_bytes >= lay.in_bytes;
+  if (!lay.line_ok) r->order = 4;
+  else if (!batched && (n == (int64_t(1) << 20) || n == (int64_t(1) << 21)))
+    r->order = tl::kOrderXcd;
+}
+
+tl_status resolve(tl::KernelId k, const tl_tune* t, const Layout& lay, int64_t n,
                   tl::Resolved* out) {
   tl::Resolved r = defaults(k, n);
-  if (t != nullptr) {
+  bool buf_ok = lay.buf_ok;
+  if (t == nullptr) {
+    default_path(k, lay, n, &r);
+  } else {
     const int l = t->lanes;
     if (l != 0 && l != 1 && l != 2 && l != 3 && l != 6 && l != 9 && l != 18)
       return fail(TL_ERR_INVALID, "tune.lanes=%d not in {0,1,2,3,6,9,18}", l);
@@ -238,7 +283,7 @@ tl_status resolve(tl::KernelId k, const tl_tune* t, bool vec_ok, bool buf_ok, in
   if (r.ppt == 4 && k != tl::KernelId::SymInverse && k != tl::KernelId::Dtg &&
       k != tl::KernelId::Generic)
     r.ppt = 2;
-  if (!vec_ok) r.ppt = 1;
+  if (!lay.vec_ok) r.ppt = 1;
   r.buf = buf_ok;
   r.num_cu = num_cus();
   *out = r;
@@ -248,7 +293,7 @@ tl_status resolve(tl::KernelId k, const tl_tune* t, bool vec_ok, bool buf_ok, in
 tl_status run(tl::KernelId k, const Checker& c, const tl_tune* tune, const tl::KArgs& a,
               void* stream) {
   tl::Resolved r;
-  tl_status s = resolve(k, tune, c.vec_ok, c.buf_ok, c.n, &r);
+  tl_status s = resolve(k, tune, c.lay, c.n, &r);
   if (s != TL_OK) return s;
   hipError_t e = r.lanes > 1
                      ? tl::launch_christoffel_lanes(r, a, c.n, static_cast<hipStream_t>(stream))
@@ -315,7 +360,7 @@ tl_status run_generated(const char* name, int64_t n, const tl_cfield* in, int32_
   for (int f = 0; f < nin; ++f) set_in(a, f, in[f]);
   for (int f = 0; f < nout; ++f) set_out(a, f, out[f]);
   Resolved r;
-  tl_status s = resolve(KernelId::Generic, tune, c.vec_ok, c.buf_ok, n, &r);
+  tl_status s = resolve(KernelId::Generic, tune, c.lay, n, &r);
   if (s != TL_OK) return s;
   hipError_t e = launch(r, a, n, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "generated kernel launch");
@@ -593,7 +638,7 @@ tl_status tl_expr(int32_t expr, int64_t n, const tl_cfield* in, int32_t nin, tl_
   for (int f = 0; f < k; ++f) set_in(a, f, in[f]);
   set_out(a, 0, out);
   tl::Resolved r;
-  tl_status s = resolve(tl::KernelId::Generic, tune, c.vec_ok, c.buf_ok, n, &r);
+  tl_status s = resolve(tl::KernelId::Generic, tune, c.lay, n, &r);
   if (s != TL_OK) return s;
   hipError_t e = tl::launch_expr(expr, r, a, n, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "expression launch");
@@ -617,7 +662,7 @@ tl_status tl_bw_twin(int64_t n, int32_t nin, tl_cfield in, int32_t nout, tl_fiel
   set_in(a, 0, in);
   set_out(a, 0, out);
   tl::Resolved r;
-  tl_status s = resolve(tl::KernelId::Generic, tune, c.vec_ok, c.buf_ok, n, &r);
+  tl_status s = resolve(tl::KernelId::Generic, tune, c.lay, n, &r);
   if (s != TL_OK) return s;
   hipError_t e = tl::launch_twin(nin, nout, r, a, n, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "twin launch");
@@ -679,15 +724,18 @@ struct PlanInput {
   std::vector<int64_t> n;
   std::vector<tl::KArgs> args;
   std::vector<Span> spans;
-  bool vec_ok = true, buf_ok = true;
+  Layout lay;
   int64_t points = 0;
   void add(int64_t nd, const tl::KArgs& a, const Checker& c) {
     n.push_back(nd);
     args.push_back(a);
     if (nd == 0) return;
     spans.insert(spans.end(), c.spans.begin(), c.spans.end());
-    vec_ok = vec_ok && c.vec_ok;
-    buf_ok = buf_ok && c.buf_ok;
+    lay.vec_ok = lay.vec_ok && c.lay.vec_ok;
+    lay.buf_ok = lay.buf_ok && c.lay.buf_ok;
+    lay.line_ok = lay.line_ok && c.lay.line_ok;
+    lay.in_bytes += c.lay.in_bytes;
+    lay.out_bytes += c.lay.out_bytes;
     points += nd;
   }
 };
@@ -714,7 +762,7 @@ tl_status plan_tables(tl::KernelId kid, PlanInput& in, const tl_tune* tune, Plan
     if (Checker::overlapping(in.spans, &a, &b))
       return fail(TL_ERR_ALIAS, "%s of one domain overlaps %s of another", a, b);
   }
-  tl_status s = resolve(kid, tune, in.vec_ok, in.buf_ok, in.points, &t->r);
+  tl_status s = resolve(kid, tune, in.lay, in.points, &t->r);
   if (s != TL_OK) return s;
   const tl::Resolved& r = t->r;
   const int32_t ndom = static_cast<int32_t>(in.n.size());
@@ -732,6 +780,10 @@ tl_status plan_tables(tl::KernelId kid, PlanInput& in, const tl_tune* tune, Plan
   }
   t->points = in.points;
   t->ntiles = t->start[ndom];
+  if (r.path == tl::Path::Staged) {
+    t->grid = tl::ordered_grid(t->ntiles > 0 ? t->ntiles : 1, r.order);
+    return TL_OK;
+  }
   int64_t blocks = t->ntiles;
   if (r.grid_mult > 0) blocks = static_cast<int64_t>(r.grid_mult) * r.num_cu;
   if (r.xcd) blocks = (blocks + 7) & ~static_cast<int64_t>(7);
@@ -964,8 +1016,9 @@ tl_status tl_kernel_info(const char* kernel, const tl_tune* tune, tl_kernel_attr
     if (std::strcmp(kExprName[e], kernel) == 0) expr = e;
   if (id == nullptr && expr < 0) return fail(TL_ERR_INVALID, "unknown kernel '%s'", kernel);
   tl::Resolved r;
-  tl_status s = resolve(id ? *id : tl::KernelId::Generic, tune, true, true, int64_t(1) << 24, &r);
+  tl_status s = resolve(id ? *id : tl::KernelId::Generic, tune, Layout{}, int64_t(1) << 24, &r);
   if (s != TL_OK) return s;
+  r.path = tl::Path::Shape;  // the kernel of the launch shape: it stores from registers
   const void* fn = id ? tl::kernel_address(*id, r) : tl::expr_address(expr, r);
   if (fn == nullptr) return fail(TL_ERR_INVALID, "no instantiation for this tuning");
   hipFuncAttributes attr;

@@ -13,6 +13,10 @@
 
 #include <cstdint>
 
+// Multiply-adds are formed within an expression as it is written, never across
+// statements: a body then rounds the same way in every kernel it runs in.
+#pragma clang fp contract(on)
+
 namespace tl {
 
 __host__ __device__ constexpr int sym(int i, int j) {

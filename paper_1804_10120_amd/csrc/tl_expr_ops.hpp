@@ -6,9 +6,9 @@
 // as B[i*3+m]; K_ij and g_ij are symmetric (s(i,j)).  Inputs are the
 // right-hand-side tensors in the order they are written; the output is the
 // left-hand side.  Bodies with 81 outputs are streaming bodies (kStream): they
-// get a loader ld(field, component) and a storer st(field, component, value) and
-// interleave loads, arithmetic and stores in program order, so that only one
-// group of outputs is live at a time.
+// get a loader ld(field, component) and a storer st(k, field, component, value)
+// for their k-th store and interleave loads, arithmetic and stores in program
+// order, so that only one group of outputs is live at a time.
 #pragma once
 
 #include "tl_device.hpp"
@@ -78,7 +78,9 @@ struct OpMult4 {
   static constexpr int NF_IN = 4, NF_OUT = 1;
   static constexpr int fin[NF_IN] = {3, 3, 3, 3};
   static constexpr int fout[NF_OUT] = {81};
-  static constexpr int NIN = 12, NOUT = 81;
+  static constexpr int NIN = 12, NOUT = 81, NST = 81;
+  static constexpr int store_f(int) { return 0; }
+  static constexpr int store_c(int k) { return k; }
   template <class L, class S>
   __device__ static inline void stream(L&& ld, S&& st) {
     double B[3], C[3], D[3], E[3];
@@ -98,7 +100,10 @@ struct OpMult4 {
         for (int k = 0; k < 3; ++k) {
           const double bcd = bc * D[k];
 #pragma unroll
-          for (int l = 0; l < 3; ++l) st(0, ((i * 3 + j) * 3 + k) * 3 + l, bcd * E[l]);
+          for (int l = 0; l < 3; ++l) {
+            const int q = ((i * 3 + j) * 3 + k) * 3 + l;
+            st(q, 0, q, bcd * E[l]);
+          }
         }
         // Keep the scheduler from forming many outputs ahead of their stores:
         // the kernel is bound by its 81 store streams, and registers held by
@@ -121,10 +126,16 @@ struct OpContract {
   static constexpr int NF_IN = M + 1, NF_OUT = 1;
   static constexpr int fin[4] = {9, M >= 2 ? 9 : 81, M >= 3 ? 9 : 81, 81};
   static constexpr int fout[NF_OUT] = {81};
-  static constexpr int NIN = 9 * M + 81, NOUT = 81;
+  static constexpr int NIN = 9 * M + 81, NOUT = 81, NST = 81;
 
-  static __device__ constexpr int e(int a, int b, int c, int d) {
+  static __host__ __device__ constexpr int e(int a, int b, int c, int d) {
     return ((a * 3 + b) * 3 + c) * 3 + d;
+  }
+  // Store order: (j,k,l,i) for one contraction, (k,l,i,j) for two, (l,k,i,j) for three.
+  static constexpr int store_f(int) { return 0; }
+  static constexpr int store_c(int q) {
+    const int d0 = q / 27, d1 = q / 9 % 3, d2 = q / 3 % 3, d3 = q % 3;
+    return M == 1 ? e(d3, d0, d1, d2) : M == 2 ? e(d2, d3, d0, d1) : e(d2, d3, d1, d0);
   }
 
   // Y = B X C^T for 3x3 matrices (X[m*3+n]).
@@ -162,7 +173,8 @@ struct OpContract {
                          e2 = ld(fE, e(2, j, k, l));
 #pragma unroll
             for (int i = 0; i < 3; ++i)
-              st(0, e(i, j, k, l), B[i * 3 + 0] * e0 + B[i * 3 + 1] * e1 + B[i * 3 + 2] * e2);
+              st(((j * 3 + k) * 3 + l) * 3 + i, 0, e(i, j, k, l),
+                 B[i * 3 + 0] * e0 + B[i * 3 + 1] * e1 + B[i * 3 + 2] * e2);
           }
     } else {
       constexpr int fC = M - 2;
@@ -183,7 +195,8 @@ struct OpContract {
 #pragma unroll
             for (int i = 0; i < 3; ++i)
 #pragma unroll
-              for (int j = 0; j < 3; ++j) st(0, e(i, j, k, l), Y[i * 3 + j]);
+              for (int j = 0; j < 3; ++j)
+                st((k * 3 + l) * 9 + i * 3 + j, 0, e(i, j, k, l), Y[i * 3 + j]);
           }
       } else {
         double D[9];
@@ -205,7 +218,7 @@ struct OpContract {
           for (int k = 0; k < 3; ++k)
 #pragma unroll
             for (int q = 0; q < 9; ++q)
-              st(0, e(q / 3, q % 3, k, l),
+              st((l * 3 + k) * 9 + q, 0, e(q / 3, q % 3, k, l),
                  D[k * 3 + 0] * Mo[0][q] + D[k * 3 + 1] * Mo[1][q] + D[k * 3 + 2] * Mo[2][q]);
         }
       }

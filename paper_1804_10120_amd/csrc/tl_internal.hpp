@@ -33,6 +33,15 @@ struct alignas(64) BatchDomain {
 enum class KernelId { SymInverse, Christoffel, CovDeriv, Dtg, Chain, ChainBwd, ChainBatched,
                       ChainFwdBwd, ChainBwdBatched, Generic };
 
+// The staged kernel (tl_stream.hpp): its block, and the components it passes
+// through LDS at a time (2 buffers x 8 x 256 doubles, 32 KB).
+constexpr int kStageBlock = 256;
+constexpr int kStageComps = 8;
+constexpr int kOrderXcd = -1;
+
+// Which kernel a call runs: the one of a launch shape, or the staged one.
+enum class Path { Shape, Staged };
+
 // A tuning request resolved to one compiled instantiation.
 struct Resolved {
   int block = 256;
@@ -43,7 +52,20 @@ struct Resolved {
   int num_cu = 256;
   bool buf = false;  // buffer addressing (every field's extent below 4 GiB)
   int lanes = 1;     // lanes per grid point (tl_christoffel only)
+  Path path = Path::Shape;
+  // of the staged kernel: loads left in the caches, the tile order
+  // (ordered_tile of tl_stream.hpp), and the LDS reserved beyond the kernel's
+  // own, which holds the blocks per compute unit down
+  bool keep_in = false;
+  int32_t order = 0;
+  uint32_t lds_pad = 0;
 };
+
+// Blocks of a launch over ntiles tiles in a given order.
+inline int64_t ordered_grid(int64_t ntiles, int32_t order) {
+  const int64_t m = order == 0 ? 1 : order == kOrderXcd ? 8 : 8 * static_cast<int64_t>(order);
+  return (ntiles + m - 1) / m * m;
+}
 
 inline int64_t grid_size(const Resolved& r, int64_t ntiles) {
   int64_t g = ntiles;

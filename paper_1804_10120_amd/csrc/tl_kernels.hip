@@ -42,6 +42,22 @@ __global__ __launch_bounds__(BLOCK) void k_batched(const BatchDomain* __restrict
   }
 }
 
+// The default kernel of a batch: k_staged (tl_stream.hpp) with the tile's
+// subgrid looked up as in k_batched.
+template <class Op, int LD>
+__global__ __launch_bounds__(kStageBlock) void k_batched_staged(
+    const BatchDomain* __restrict__ doms, const int64_t* __restrict__ start,
+    const int32_t* __restrict__ tile_dom, int64_t ntiles, int32_t order) {
+  __shared__ double buf[2][kStageComps][kStageBlock];
+  const int64_t t = ordered_tile(order);
+  if (t >= ntiles) return;
+  const int32_t d = tile_dom[t];
+  const KArgs a = doms[d].args;
+  const int64_t n = doms[d].n;
+  const Bufs<Op> b = make_bufs<Op>(a, n);
+  tile_staged<Op, LD>(buf, a, b, n, (t - start[d]) * kStageBlock);
+}
+
 __global__ void k_copy(const double* __restrict__ src, double* __restrict__ dst, int64_t n) {
   const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x * 2;
   for (int64_t i = (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) * 2; i < n;
@@ -215,9 +231,28 @@ const void* kernel_address(KernelId k, const Resolved& r) {
   }
 }
 
+template <class Op>
+static const void* ptr_batched_staged(const Resolved& r) {
+  return r.keep_in ? reinterpret_cast<const void*>(&k_batched_staged<Op, 0>)
+                   : reinterpret_cast<const void*>(&k_batched_staged<Op, kCpolNT>);
+}
+
 hipError_t launch_batched(KernelId k, const Resolved& r, const BatchDomain* doms, const int64_t* start,
                           const int32_t* tile_dom, int64_t ntiles, int64_t grid, int64_t chunk,
                           hipStream_t s) {
+  if (r.path == Path::Staged) {
+    const void* fn = k == KernelId::ChainBatched      ? ptr_batched_staged<OpChain>(r)
+                     : k == KernelId::ChainBwdBatched ? ptr_batched_staged<OpChainBwd>(r)
+                                                      : nullptr;
+    if (fn == nullptr) return hipErrorInvalidValue;
+    int32_t order = r.order;
+    void* args[] = {const_cast<BatchDomain**>(&doms), const_cast<int64_t**>(&start),
+                    const_cast<int32_t**>(&tile_dom), &ntiles, &order};
+    hipError_t e = hipLaunchKernel(fn, dim3(static_cast<unsigned>(grid)), dim3(kStageBlock), args,
+                                   r.lds_pad, s);
+    if (e != hipSuccess) return e;
+    return hipGetLastError();
+  }
   const void* fn = ptr_batched(k, r);
   if (fn == nullptr) return hipErrorInvalidValue;
   int32_t xcd = r.xcd ? 1 : 0;

@@ -12,10 +12,12 @@
 // the instructions spent on addresses (buffer addressing, below).
 //
 // A body with more outputs than registers comfortably hold (kStream) is
-// instead given a loader ld(field, component) and a storer st(field,
-// component, value) and interleaves its own loads, math and stores in program
-// order, one point per lane; stores are never moved above later loads, so
-// only one group of outputs is live at a time.
+// instead given a loader ld(field, component) and a storer st(k, field,
+// component, value), k counting its stores from 0, and interleaves its own
+// loads, math and stores in program order, one point per lane; stores are
+// never moved above later loads, so only one group of outputs is live at a
+// time.  The body also names the field and component of its k-th store
+// (store_f, store_c) and their number (NST).
 //
 // A tile is BLOCK*PPT consecutive points; a block walks tiles
 // logical_block, logical_block + gridDim.x, ... so the same kernel serves a
@@ -25,8 +27,11 @@
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
+#include <utility>
 
 #include "tl_internal.hpp"
+
+#pragma clang fp contract(on)  // as in tl_device.hpp: a body rounds alike in every kernel
 
 namespace tl {
 
@@ -149,7 +154,7 @@ constexpr int op_ppt(int ppt) {
 template <class Op, bool NT>
 __device__ inline void point_stream(const KArgs& a, int64_t p) {
   Op::stream([&](int f, int c) { return load1<NT>(a.in[f] + c * a.ldin[f] + p); },
-             [&](int f, int c, double v) { store1<NT>(a.out[f] + c * a.ldout[f] + p, v); });
+             [&](int, int f, int c, double v) { store1<NT>(a.out[f] + c * a.ldout[f] + p, v); });
 }
 
 // Points p .. p+PPT-1 of one tile, all in range.
@@ -256,7 +261,7 @@ __device__ inline Bufs<Op> make_bufs(const KArgs& a, int64_t n) {
 template <class Op, bool NT>
 __device__ inline void point_stream_buf(const Bufs<Op>& b, uint32_t p8) {
   Op::stream([&](int f, int c) { return bload1<NT>(b.in[f], p8, c * b.ldin8[f]); },
-             [&](int f, int c, double v) { bstore1<NT>(b.out[f], p8, c * b.ldout8[f], v); });
+             [&](int, int f, int c, double v) { bstore1<NT>(b.out[f], p8, c * b.ldout8[f], v); });
 }
 
 template <class Op, int PPT, bool NT>
@@ -390,6 +395,186 @@ __global__ __launch_bounds__(BLOCK) void k_points(KArgs a, int64_t n, int64_t nt
   }
 }
 
+// ---- Staged kernel: the default of large grids, and of grids of any size whose
+// output components do not start on 128-byte lines.
+//
+// Buffer cache policies (the aux operand): 0 keeps a line in the caches,
+// kCpolNT streams past them.
+template <int CPOL>
+__device__ inline double cload(rsrc_t r, uint32_t voff, uint32_t soff) {
+  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, CPOL));
+}
+template <int CPOL>
+__device__ inline void cstore(rsrc_t r, uint32_t voff, uint32_t soff, double v) {
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, soff, CPOL);
+}
+
+// Tile of a block.  Workgroups go to the 8 XCDs round-robin (block b to XCD
+// b % 8).  order 0: tile b; kOrderXcd: each XCD takes one contiguous range of
+// tiles (the grid is a multiple of 8); R > 0: the XCDs take runs of R tiles in
+// turn (the grid is a multiple of 8 R).
+__device__ inline int64_t ordered_tile(int32_t order) {
+  const int64_t b = blockIdx.x;
+  if (order == 0) return b;
+  if (order == kOrderXcd) return (b & 7) * (static_cast<int64_t>(gridDim.x) >> 3) + (b >> 3);
+  const int64_t s = b >> 3, run = s / order;
+  return (run * 8 + (b & 7)) * order + (s - run * order);
+}
+
+// A barrier that orders the block's LDS accesses only: loads and stores to
+// memory stay in flight across it.
+__device__ inline void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The stores of a body in program order: field and component of each.
+template <class Op>
+constexpr int num_stores() {
+  if constexpr (is_stream<Op>::value) return Op::NST;
+  else return Op::NOUT;
+}
+template <int N>
+struct StoreList {
+  int f[N], c[N];
+};
+template <class Op>
+constexpr StoreList<num_stores<Op>()> store_list() {
+  StoreList<num_stores<Op>()> l{};
+  if constexpr (is_stream<Op>::value) {
+    for (int k = 0; k < Op::NST; ++k) {
+      l.f[k] = Op::store_f(k);
+      l.c[k] = Op::store_c(k);
+    }
+  } else {
+    int k = 0;
+    for (int f = 0; f < Op::NF_OUT; ++f)
+      for (int c = 0; c < Op::fout[f]; ++c, ++k) {
+        l.f[k] = f;
+        l.c[k] = c;
+      }
+  }
+  return l;
+}
+
+// Outputs of a tile staged through LDS, kStageComps components at a time, and
+// stored line by line.  Bound by HBM bandwidth like the kernels above; what
+// they lose is in the stores.  With an odd leading dimension no component of a
+// tile starts on a 128-byte line, and a wave that stores its own 64 points
+// writes two partial lines of the five it touches, which memory has to merge.
+// Here thread i stores point (i + a) mod 256 of a component, a being the
+// distance from the tile's start to the component's first line, so the first
+// 240 threads store whole lines past the caches and only the last 16 the
+// tile's two ends, left in the L2, where the neighbouring tile's part joins
+// them (so the neighbour runs on the same XCD: runs of 4 tiles).  Measured,
+// stores from registers / staged: the adjoint over 159^3 points with ld = n
+// 643 / 504 us, over 127^3 328 / 266 us; forward and adjoint in one pass over
+// 159^3 785 / 600 us; Gamma over 127^3 148 / 130 us; the three contractions
+// over 65^3 118 / 84 us.
+// Fully aligned grids gain too, from fewer waves: a block's stores of a
+// component leave together, and with two blocks of 256 per compute unit (the
+// launch reserves LDS for that) instead of five fewer streams meet in memory.
+// Over 160^3 points the adjoint takes 519 us from registers, 508 staged with
+// three blocks per unit and 493 with two; the forward 279, 277 and 271; one
+// block too few and the reads no longer cover their latency (blocks of 64,
+// three per unit: 745).
+// 8 components a time, 32 KB: 16 measured the same at two blocks per unit.
+// Two buffers, so one barrier per group: a group is written to the buffer that
+// the group before last was read from, and that read ended before the last
+// barrier.
+template <class Op>
+struct Stage {
+  double (*buf)[kStageComps][kStageBlock];
+  const KArgs& a;
+  const Bufs<Op>& b;
+  int64_t p0;     // first point of the tile
+  uint32_t left;  // points of the tile
+
+  // The k-th value; k is a constant once the body is unrolled.
+  __device__ __forceinline__ void put(int k, double v) const {
+    buf[(k / kStageComps) & 1][k % kStageComps][threadIdx.x] = v;
+    if (k % kStageComps == kStageComps - 1 || k == num_stores<Op>() - 1) {
+      lds_barrier();
+      flush(k / kStageComps, std::make_integer_sequence<int, kStageComps>{});
+    }
+  }
+  template <int... Q>
+  __device__ __forceinline__ void flush(int g, std::integer_sequence<int, Q...>) const {
+    (store(g * kStageComps + Q), ...);
+  }
+  __device__ __forceinline__ void store(int k) const {
+    constexpr auto list = store_list<Op>();
+    if (k >= num_stores<Op>()) return;
+    const int f = list.f[k], c = list.c[k];
+    if constexpr (!is_stream<Op>::value)
+      if (a.out[f] == nullptr) return;
+    const uint32_t at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(a.out[f]) >> 3) +
+                        static_cast<uint32_t>(c) * static_cast<uint32_t>(a.ldout[f]) +
+                        static_cast<uint32_t>(p0);
+    const uint32_t first = (0u - at) & 15u;
+    const uint32_t e = (threadIdx.x + first) & (kStageBlock - 1);
+    const double v = buf[(k / kStageComps) & 1][k % kStageComps][e];
+    if (e < left) {
+      const uint32_t off = static_cast<uint32_t>(p0 + e) * 8u;
+      if (first == 0 || threadIdx.x < kStageBlock - 16)
+        cstore<kCpolNT>(b.out[f], off, c * b.ldout8[f], v);
+      else
+        cstore<0>(b.out[f], off, c * b.ldout8[f], v);
+    }
+  }
+  template <int... K>
+  __device__ __forceinline__ void put_all(const double* y, std::integer_sequence<int, K...>) const {
+    (put(K, y[K]), ...);
+  }
+};
+
+// The points of one tile, n - p0 or more of them: every thread loads (the last
+// point again where the tile is short), because all take part in the staging.
+template <class Op, int LD>
+__device__ inline void tile_staged(double (*buf)[kStageComps][kStageBlock], const KArgs& a,
+                                   const Bufs<Op>& b, int64_t n, int64_t p0) {
+  const int64_t p = p0 + threadIdx.x;
+  const uint32_t p8 = static_cast<uint32_t>((p < n ? p : n - 1) * 8);
+  const Stage<Op> stage{buf, a, b, p0,
+                            static_cast<uint32_t>(n - p0 < kStageBlock ? n - p0 : kStageBlock)};
+  const auto ld = [&](int f, int c) { return cload<LD>(b.in[f], p8, c * b.ldin8[f]); };
+  if constexpr (is_stream<Op>::value) {
+    Op::stream(ld, [&](int k, int, int, double v) { stage.put(k, v); });
+  } else {
+    constexpr auto io = in_offsets<Op>();
+    double x[Op::NIN], y[Op::NOUT];
+#pragma unroll
+    for (int f = 0; f < Op::NF_IN; ++f)
+#pragma unroll
+      for (int c = 0; c < Op::fin[f]; ++c) x[io.v[f] + c] = ld(f, c);
+    Op::apply(x, y);
+    stage.put_all(y, std::make_integer_sequence<int, Op::NOUT>{});
+  }
+}
+
+template <class Op, int LD>
+__global__ __launch_bounds__(kStageBlock) void k_staged(KArgs a, int64_t n, int64_t ntiles,
+                                                        int32_t order) {
+  __shared__ double buf[2][kStageComps][kStageBlock];
+  const int64_t t = ordered_tile(order);
+  if (t >= ntiles) return;
+  const Bufs<Op> b = make_bufs<Op>(a, n);
+  tile_staged<Op, LD>(buf, a, b, n, t * kStageBlock);
+}
+
+template <class Op, int LD>
+static hipError_t launch_staged_p(const Resolved& r, const KArgs& a, int64_t n, hipStream_t s) {
+  const int64_t ntiles = (n + kStageBlock - 1) / kStageBlock;
+  hipLaunchKernelGGL((k_staged<Op, LD>), dim3(static_cast<unsigned>(ordered_grid(ntiles, r.order))),
+                     dim3(kStageBlock), r.lds_pad, s, a, n, ntiles, r.order);
+  return hipGetLastError();
+}
+
+template <class Op>
+static hipError_t launch_staged(const Resolved& r, const KArgs& a, int64_t n, hipStream_t s) {
+  return r.keep_in ? launch_staged_p<Op, 0>(r, a, n, s) : launch_staged_p<Op, kCpolNT>(r, a, n, s);
+}
 
 template <class Op, int BLOCK, int PPT, bool NT, bool BUF>
 static const void* kernel_ptr() {
@@ -438,6 +623,7 @@ static Resolved clamp_block(const Resolved& r0) {
 
 template <class Op>
 static hipError_t launch_op(const Resolved& r0, const KArgs& a, int64_t n, hipStream_t s) {
+  if (r0.path == Path::Staged) return launch_staged<Op>(r0, a, n, s);
   const Resolved r = clamp_block<Op>(r0);
   const int64_t per = static_cast<int64_t>(r.block) * op_ppt<Op>(r.ppt);
   const int64_t ntiles = (n + per - 1) / per;
