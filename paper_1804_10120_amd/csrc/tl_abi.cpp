@@ -211,37 +211,64 @@ tl::Resolved defaults(tl::KernelId k, int64_t n) {
   return r;
 }
 
-// The kernel of a call that gives no launch shape: the staged one
-// (tl_stream.hpp, with what it measured) where it is the faster.
-//  - From 2^19 points: with whole lines the two kernels are within 1 % at 80^3
-//    and 97^3 points, and the staged one takes 2-5 % less from 2^21.  It then
-//    runs two blocks per compute unit (24 KB of LDS reserved beside its 32).
-//  - From 2^16 points if an output component does not start on a line: 45^3
-//    points are a draw, at 61^3 the adjoint takes 26.2 us against 29.7 us.
-//    Blocks are not held down below 2^19, where they would not fill the chip.
-//    The same for a batch, whose subgrids are ragged as a rule: 195 k points in
-//    48 aligned subgrids are a draw.
+// The kernel of a call that gives no launch shape (tl_stream.hpp), its tile
+// order and cache policies.  Figures: two or three buffer sets in turn, HIP
+// events, one run; "ragged": an output component that does not start on a line.
+//
+// Staged (what it gains stands at Stage) from 2^20 points, where the adjoint
+// over 159^3 aligned points takes 483 us against 502 from registers, the forward
+// 267 / 278, and below 100^3 the two are within 2 %; if ragged from 2^16 points
+// (45^3 is a draw, at 61^3 the adjoint takes 26.2 / 29.7 us), and the same for
+// a batch, whose subgrids are ragged as a rule.  At exactly 2^20 and 2^21
+// aligned points the kernel with one tile range per XCD stays (Gamma over 128^3
+// 117 us against 120 staged in that order, the forward 134 / 135).  Otherwise
+// one point per lane in blocks of 64, stored from registers, which at 33^3 to
+// 80^3 is the fastest or within 2 % of it.
+// Two blocks per compute unit (24 KB of LDS reserved beside the kernel's 32)
+// only for bodies of at least 32 component streams: with 12 the few loads in
+// flight no longer cover their latency (the inverse over 159^3 82 us against
+// 64), with 39 the covariant derivative takes 206 against 217.  Ragged grids
+// gain from it from 2^19 points on (the adjoint over 79^3 66.6 / 68.6 us).
 // Tile order: runs of 4 tiles per XCD where tiles share lines (at 159^3 points
 // the adjoint takes 549, 534, 534 and 528 us in plain order and in runs of 4,
-// 8 and 16, Gamma 241, 240, 243 and 241 us); one range per XCD at exactly 2^20
-// and 2^21 points, as for defaults() above; else plain order, which at 160^3
+// 8 and 16, Gamma 241, 240, 243 and 241 us); else plain order, which at 160^3
 // beats runs of 4 by 1-4 %.
-// Loads stay in the L2 where the lines are shared and the body writes at least
-// half of what it reads: the adjoint over 159^3 points takes 504 us with them,
-// 534 without; Gamma 243 and 240, the forward 290 and 285 us (which reads seven
-// times what it writes, and keeps streaming).
+//
+// Cache policies.  The Infinity Cache (256 MiB) is worth using only for what
+// stays in it until its next use, so a call keeps at most a share of it:
+//  - inputs of at most 96 MiB are loaded through the caches: with three sets in
+//    turn the adjoint over 57^3 points takes 19.3 us against 23 streamed, the
+//    inverse over 100^3 14.8 / 17.7; with six sets, which do not fit, 4 % more;
+//  - outputs are left in the cache beside them only up to 32 MiB in all (at
+//    62 MB Gamma takes 10.3 us against 10.7 with three sets, 14.9 against 10.7
+//    with six);
+//  - with inputs beyond 96 MiB, outputs of at most 64 MiB are kept (the forward
+//    over 112^3 points 96 us against 101, d_t g over 97^3 26.7 / 29.4), for the
+//    next kernel to find.
+// Ragged tiles share lines with their neighbours on the same XCD, and where a
+// body writes about as much as it reads and moves a lot, loads left in the L2
+// pay: the adjoint over 159^3 points 504 us against 534, the three contractions
+// over 127^3 613 / 628; with less in flight they do not (Gamma 243 / 240, the
+// three contractions over 97^3 276 / 275, assign3 over 127^3 172 / 166).
 void default_path(tl::KernelId k, const Layout& lay, int64_t n, tl::Resolved* r) {
   const bool batched = k == tl::KernelId::ChainBatched || k == tl::KernelId::ChainBwdBatched;
-  const int64_t few = int64_t(1) << 16, many = int64_t(1) << 19;
-  if (!lay.buf_ok || n < few || (n < many && lay.line_ok && !batched)) return;
-  r->path = tl::Path::Staged;
-  r->block = tl::kStageBlock;
+  const int64_t p16 = int64_t(1) << 16, p19 = int64_t(1) << 19, p20 = int64_t(1) << 20;
+  const int64_t in = lay.in_bytes >> 20, out = lay.out_bytes >> 20;  // MiB
+  if (!lay.buf_ok || (batched && n < p16)) return;
+  if (lay.line_ok && !batched && (n == p20 || n == 2 * p20)) return;
   r->ppt = 1;
-  r->lds_pad = n >= many ? 24 << 10 : 0;
-  r->keep_in = !lay.line_ok && 2 * lay.out_bytes >= lay.in_bytes;
-  if (!lay.line_ok) r->order = 4;
-  else if (!batched && (n == (int64_t(1) << 20) || n == (int64_t(1) << 21)))
-    r->order = tl::kOrderXcd;
+  if (n >= p20 || (n >= p16 && (batched || !lay.line_ok))) {
+    r->path = tl::Path::Staged;
+    r->block = tl::kStageBlock;
+    if (n >= (lay.line_ok ? p20 : p19) && lay.in_bytes + lay.out_bytes >= 32 * 8 * n)
+      r->lds_pad = 24 << 10;
+    if (!lay.line_ok) r->order = 4;
+  } else {
+    r->path = tl::Path::Small;
+    r->block = tl::kSmallBlock;
+  }
+  r->keep_in = in < 96 || (!lay.line_ok && in >= 512 && 4 * out >= 3 * in);
+  r->keep_out = in + out < 32 || (in >= 96 && out < 64);
 }
 
 tl_status resolve(tl::KernelId k, const tl_tune* t, const Layout& lay, int64_t n,

@@ -38,9 +38,10 @@ enum class KernelId { SymInverse, Christoffel, CovDeriv, Dtg, Chain, ChainBwd, C
 constexpr int kStageBlock = 256;
 constexpr int kStageComps = 8;
 constexpr int kOrderXcd = -1;
+constexpr int kSmallBlock = 64;  // block of k_small
 
-// Which kernel a call runs: the one of a launch shape, or the staged one.
-enum class Path { Shape, Staged };
+// Which kernel a call runs: the one of a launch shape, or one of the defaults.
+enum class Path { Shape, Small, Staged };
 
 // A tuning request resolved to one compiled instantiation.
 struct Resolved {
@@ -53,10 +54,11 @@ struct Resolved {
   bool buf = false;  // buffer addressing (every field's extent below 4 GiB)
   int lanes = 1;     // lanes per grid point (tl_christoffel only)
   Path path = Path::Shape;
-  // of the staged kernel: loads left in the caches, the tile order
-  // (ordered_tile of tl_stream.hpp), and the LDS reserved beyond the kernel's
-  // own, which holds the blocks per compute unit down
-  bool keep_in = false;
+  // of the default kernels: inputs and outputs left in the caches; of the
+  // staged one: the tile order (ordered_tile of tl_stream.hpp), and the LDS
+  // reserved beyond the kernel's own, which holds the blocks per compute unit
+  // down
+  bool keep_in = false, keep_out = false;
   int32_t order = 0;
   uint32_t lds_pad = 0;
 };

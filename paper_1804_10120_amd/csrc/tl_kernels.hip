@@ -44,7 +44,7 @@ __global__ __launch_bounds__(BLOCK) void k_batched(const BatchDomain* __restrict
 
 // The default kernel of a batch: k_staged (tl_stream.hpp) with the tile's
 // subgrid looked up as in k_batched.
-template <class Op, int LD>
+template <class Op, int LD, int ST>
 __global__ __launch_bounds__(kStageBlock) void k_batched_staged(
     const BatchDomain* __restrict__ doms, const int64_t* __restrict__ start,
     const int32_t* __restrict__ tile_dom, int64_t ntiles, int32_t order) {
@@ -55,7 +55,7 @@ __global__ __launch_bounds__(kStageBlock) void k_batched_staged(
   const KArgs a = doms[d].args;
   const int64_t n = doms[d].n;
   const Bufs<Op> b = make_bufs<Op>(a, n);
-  tile_staged<Op, LD>(buf, a, b, n, (t - start[d]) * kStageBlock);
+  tile_staged<Op, LD, ST>(buf, a, b, n, (t - start[d]) * kStageBlock);
 }
 
 __global__ void k_copy(const double* __restrict__ src, double* __restrict__ dst, int64_t n) {
@@ -233,8 +233,9 @@ const void* kernel_address(KernelId k, const Resolved& r) {
 
 template <class Op>
 static const void* ptr_batched_staged(const Resolved& r) {
-  return r.keep_in ? reinterpret_cast<const void*>(&k_batched_staged<Op, 0>)
-                   : reinterpret_cast<const void*>(&k_batched_staged<Op, kCpolNT>);
+#define TL_PTR(LD, ST) reinterpret_cast<const void*>(&k_batched_staged<Op, LD, ST>)
+  return TL_BY_POLICY(r, TL_PTR);
+#undef TL_PTR
 }
 
 hipError_t launch_batched(KernelId k, const Resolved& r, const BatchDomain* doms, const int64_t* start,

@@ -395,11 +395,15 @@ __global__ __launch_bounds__(BLOCK) void k_points(KArgs a, int64_t n, int64_t nt
   }
 }
 
-// ---- Staged kernel: the default of large grids, and of grids of any size whose
-// output components do not start on 128-byte lines.
+// ---- Default kernels: a call that gives no launch shape runs k_small or
+// k_staged; the rule and the policies stand at default_path in tl_abi.cpp.
 //
 // Buffer cache policies (the aux operand): 0 keeps a line in the caches,
-// kCpolNT streams past them.
+// kCpolNT streams past them, kCpolDev (device scope) sends a store through the
+// L2 at once and leaves it in the Infinity Cache, so nothing is left to write
+// back when the kernel ends.
+constexpr int kCpolDev = 16;
+
 template <int CPOL>
 __device__ inline double cload(rsrc_t r, uint32_t voff, uint32_t soff) {
   return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, CPOL));
@@ -419,6 +423,38 @@ __device__ inline int64_t ordered_tile(int32_t order) {
   if (order == kOrderXcd) return (b & 7) * (static_cast<int64_t>(gridDim.x) >> 3) + (b >> 3);
   const int64_t s = b >> 3, run = s / order;
   return (run * 8 + (b & 7)) * order + (s - run * order);
+}
+
+// Small grids: one point per lane in blocks of 64, so that even a few thousand
+// points spread over the chip, stored from registers.
+template <class Op, int LD, int ST>
+__global__ __launch_bounds__(kSmallBlock) void k_small(KArgs a, int64_t n) {
+  const Bufs<Op> b = make_bufs<Op>(a, n);
+  const int64_t p = static_cast<int64_t>(blockIdx.x) * kSmallBlock + threadIdx.x;
+  if (p >= n) return;
+  const uint32_t p8 = static_cast<uint32_t>(p * 8);
+  const auto ld = [&](int f, int c) { return cload<LD>(b.in[f], p8, c * b.ldin8[f]); };
+  if constexpr (is_stream<Op>::value) {
+    Op::stream(ld, [&](int, int f, int c, double v) {
+      cstore<ST>(b.out[f], p8, c * b.ldout8[f], v);
+    });
+  } else {
+    constexpr auto io = in_offsets<Op>();
+    constexpr auto oo = out_offsets<Op>();
+    double x[Op::NIN], y[Op::NOUT];
+#pragma unroll
+    for (int f = 0; f < Op::NF_IN; ++f)
+#pragma unroll
+      for (int c = 0; c < Op::fin[f]; ++c) x[io.v[f] + c] = ld(f, c);
+    Op::apply(x, y);
+#pragma unroll
+    for (int f = 0; f < Op::NF_OUT; ++f) {
+      if (a.out[f] == nullptr) continue;
+#pragma unroll
+      for (int c = 0; c < Op::fout[f]; ++c)
+        cstore<ST>(b.out[f], p8, c * b.ldout8[f], y[oo.v[f] + c]);
+    }
+  }
 }
 
 // A barrier that orders the block's LDS accesses only: loads and stores to
@@ -483,7 +519,7 @@ constexpr StoreList<num_stores<Op>()> store_list() {
 // Two buffers, so one barrier per group: a group is written to the buffer that
 // the group before last was read from, and that read ended before the last
 // barrier.
-template <class Op>
+template <class Op, int ST>
 struct Stage {
   double (*buf)[kStageComps][kStageBlock];
   const KArgs& a;
@@ -518,7 +554,7 @@ struct Stage {
     if (e < left) {
       const uint32_t off = static_cast<uint32_t>(p0 + e) * 8u;
       if (first == 0 || threadIdx.x < kStageBlock - 16)
-        cstore<kCpolNT>(b.out[f], off, c * b.ldout8[f], v);
+        cstore<ST>(b.out[f], off, c * b.ldout8[f], v);
       else
         cstore<0>(b.out[f], off, c * b.ldout8[f], v);
     }
@@ -531,12 +567,12 @@ struct Stage {
 
 // The points of one tile, n - p0 or more of them: every thread loads (the last
 // point again where the tile is short), because all take part in the staging.
-template <class Op, int LD>
+template <class Op, int LD, int ST>
 __device__ inline void tile_staged(double (*buf)[kStageComps][kStageBlock], const KArgs& a,
                                    const Bufs<Op>& b, int64_t n, int64_t p0) {
   const int64_t p = p0 + threadIdx.x;
   const uint32_t p8 = static_cast<uint32_t>((p < n ? p : n - 1) * 8);
-  const Stage<Op> stage{buf, a, b, p0,
+  const Stage<Op, ST> stage{buf, a, b, p0,
                             static_cast<uint32_t>(n - p0 < kStageBlock ? n - p0 : kStageBlock)};
   const auto ld = [&](int f, int c) { return cload<LD>(b.in[f], p8, c * b.ldin8[f]); };
   if constexpr (is_stream<Op>::value) {
@@ -553,27 +589,41 @@ __device__ inline void tile_staged(double (*buf)[kStageComps][kStageBlock], cons
   }
 }
 
-template <class Op, int LD>
+template <class Op, int LD, int ST>
 __global__ __launch_bounds__(kStageBlock) void k_staged(KArgs a, int64_t n, int64_t ntiles,
                                                         int32_t order) {
   __shared__ double buf[2][kStageComps][kStageBlock];
   const int64_t t = ordered_tile(order);
   if (t >= ntiles) return;
   const Bufs<Op> b = make_bufs<Op>(a, n);
-  tile_staged<Op, LD>(buf, a, b, n, t * kStageBlock);
+  tile_staged<Op, LD, ST>(buf, a, b, n, t * kStageBlock);
 }
 
-template <class Op, int LD>
-static hipError_t launch_staged_p(const Resolved& r, const KArgs& a, int64_t n, hipStream_t s) {
-  const int64_t ntiles = (n + kStageBlock - 1) / kStageBlock;
-  hipLaunchKernelGGL((k_staged<Op, LD>), dim3(static_cast<unsigned>(ordered_grid(ntiles, r.order))),
-                     dim3(kStageBlock), r.lds_pad, s, a, n, ntiles, r.order);
+// LAUNCH(LD, ST) with the launch's cache policies.
+#define TL_BY_POLICY(r, LAUNCH)                                        \
+  ((r).keep_in ? ((r).keep_out ? LAUNCH(0, kCpolDev) : LAUNCH(0, kCpolNT)) \
+               : ((r).keep_out ? LAUNCH(kCpolNT, kCpolDev) : LAUNCH(kCpolNT, kCpolNT)))
+
+template <class Op, int LD, int ST>
+static hipError_t launch_default_p(const Resolved& r, const KArgs& a, int64_t n, hipStream_t s) {
+  if (r.path == Path::Small) {
+    const int64_t grid = (n + kSmallBlock - 1) / kSmallBlock;
+    hipLaunchKernelGGL((k_small<Op, LD, ST>), dim3(static_cast<unsigned>(grid)), dim3(kSmallBlock),
+                       0, s, a, n);
+  } else {
+    const int64_t ntiles = (n + kStageBlock - 1) / kStageBlock;
+    hipLaunchKernelGGL((k_staged<Op, LD, ST>),
+                       dim3(static_cast<unsigned>(ordered_grid(ntiles, r.order))),
+                       dim3(kStageBlock), r.lds_pad, s, a, n, ntiles, r.order);
+  }
   return hipGetLastError();
 }
 
 template <class Op>
-static hipError_t launch_staged(const Resolved& r, const KArgs& a, int64_t n, hipStream_t s) {
-  return r.keep_in ? launch_staged_p<Op, 0>(r, a, n, s) : launch_staged_p<Op, kCpolNT>(r, a, n, s);
+static hipError_t launch_default(const Resolved& r, const KArgs& a, int64_t n, hipStream_t s) {
+#define TL_LAUNCH(LD, ST) launch_default_p<Op, LD, ST>(r, a, n, s)
+  return TL_BY_POLICY(r, TL_LAUNCH);
+#undef TL_LAUNCH
 }
 
 template <class Op, int BLOCK, int PPT, bool NT, bool BUF>
@@ -623,7 +673,7 @@ static Resolved clamp_block(const Resolved& r0) {
 
 template <class Op>
 static hipError_t launch_op(const Resolved& r0, const KArgs& a, int64_t n, hipStream_t s) {
-  if (r0.path == Path::Staged) return launch_staged<Op>(r0, a, n, s);
+  if (r0.path != Path::Shape) return launch_default<Op>(r0, a, n, s);
   const Resolved r = clamp_block<Op>(r0);
   const int64_t per = static_cast<int64_t>(r.block) * op_ppt<Op>(r.ppt);
   const int64_t ntiles = (n + per - 1) / per;

@@ -1,8 +1,9 @@
-"""The kernel that stages its outputs through LDS (the default of large and of
-ragged grids) against the kernels that store from registers, which the parity
-tests hold to the oracle: the same bodies, so bitwise the same buffers,
-everything around the fields included.  Sizes and layouts at the edges of its
-rule and of its tiles (256 points, lines of 16 doubles)."""
+"""The kernels a call without a launch shape runs -- outputs staged through LDS on
+large and on ragged grids, else one point per lane in blocks of 64, each with
+the cache policies of its size -- against the kernels of a given shape, which
+the parity tests hold to the oracle: the same bodies, so bitwise the same
+buffers, everything around the fields included.  Sizes and layouts at the edges
+of the rule and of the staged tiles (256 points, lines of 16 doubles)."""
 import pytest
 import torch
 
@@ -20,7 +21,7 @@ BWD = ("g", "dg", "beta", "K", "alpha", "w")
 # (n, leading-dimension padding or None for whole lines, offset of the field in its buffer)
 LAYOUTS = [(2 ** 16, 1, 0), (2 ** 16 + 1, 0, 3), (2 ** 16 + 255, 13, 15), (2 ** 16 + 256, 8, 0),
            (2 ** 19 - 1, 0, 0), (2 ** 19, None, 0), (2 ** 19 + 17, None, 0), (2 ** 19 + 241, 7, 1),
-           (2 ** 20, None, 0)]
+           (2 ** 20, None, 0), (2 ** 20 + 1, None, 0), (2 ** 20 + 243, 1, 0)]
 IDS = [f"n{n}pad{p}off{o}" for n, p, o in LAYOUTS]
 
 
