@@ -151,7 +151,8 @@ tl_status tl_dtg_chain(int64_t n, tl_cfield g, tl_cfield dg, tl_cfield beta, tl_
  * g^ij and b^l are recomputed, not stored.  d beta is not an input: d_t g is
  * linear in it, so its gradient depends on w only.  An output whose ptr is
  * NULL is skipped (ld ignored); at least one output must be non-NULL.
- * Reads 40 and writes up to 43 doubles per point. */
+ * Reads up to 40 and writes up to 43 doubles per point: with tune NULL an input
+ * field that no requested gradient depends on is not read. */
 tl_status tl_dtg_chain_bwd(int64_t n, tl_cfield g, tl_cfield dg, tl_cfield beta, tl_cfield K,
                            tl_cfield alpha, tl_cfield w, tl_field g_bar, tl_field dg_bar,
                            tl_field beta_bar, tl_field dbeta_bar, tl_field K_bar,

@@ -15,6 +15,7 @@
 #include <string>
 #include <vector>
 
+#include "tl_device.hpp"
 #include "tl_internal.hpp"
 
 namespace {
@@ -51,7 +52,8 @@ struct Layout {
   bool vec_ok = true;   // every field 16-byte aligned with even ld (for ppt = 2)
   bool buf_ok = true;   // every field spans less than 4 GiB (32-bit buffer offsets)
   bool line_ok = true;  // every output component starts on a 128-byte line
-  int64_t in_bytes = 0, out_bytes = 0;
+  bool partial = false;  // an output is left out, and with it the inputs only it needs
+  int64_t in_bytes = 0, out_bytes = 0;  // of the fields of the call
 };
 
 struct Checker {
@@ -66,7 +68,10 @@ struct Checker {
              bool optional = false) {
     if (st != TL_OK) return;
     if (ptr == nullptr) {
-      if (optional) return;
+      if (optional) {
+        lay.partial = true;
+        return;
+      }
       st = fail(TL_ERR_NULL, "%s is NULL", name);
       return;
     }
@@ -221,7 +226,8 @@ tl::Resolved defaults(tl::KernelId k, int64_t n) {
 // (45^3 is a draw, at 61^3 the adjoint takes 26.2 / 29.7 us), and the same for
 // a batch, whose subgrids are ragged as a rule.  At exactly 2^20 and 2^21
 // aligned points the kernel with one tile range per XCD stays (Gamma over 128^3
-// 117 us against 120 staged in that order, the forward 134 / 135).  Otherwise
+// 117 us against 120 staged in that order, the forward 134 / 135), unless
+// outputs are left out: only the default kernels skip the inputs of those.  Otherwise
 // one point per lane in blocks of 64, stored from registers, which at 33^3 to
 // 80^3 is the fastest or within 2 % of it.
 // Two blocks per compute unit (24 KB of LDS reserved beside the kernel's 32)
@@ -255,14 +261,15 @@ void default_path(tl::KernelId k, const Layout& lay, int64_t n, tl::Resolved* r)
   const int64_t p16 = int64_t(1) << 16, p19 = int64_t(1) << 19, p20 = int64_t(1) << 20;
   const int64_t in = lay.in_bytes >> 20, out = lay.out_bytes >> 20;  // MiB
   if (!lay.buf_ok || (batched && n < p16)) return;
-  if (lay.line_ok && !batched && (n == p20 || n == 2 * p20)) return;
+  const bool xcd = lay.line_ok && !batched && (n == p20 || n == 2 * p20);
+  if (xcd && !lay.partial) return;
   r->ppt = 1;
   if (n >= p20 || (n >= p16 && (batched || !lay.line_ok))) {
     r->path = tl::Path::Staged;
     r->block = tl::kStageBlock;
     if (n >= (lay.line_ok ? p20 : p19) && lay.in_bytes + lay.out_bytes >= 32 * 8 * n)
       r->lds_pad = 24 << 10;
-    if (!lay.line_ok) r->order = 4;
+    r->order = xcd ? tl::kOrderXcd : lay.line_ok ? 0 : 4;
   } else {
     r->path = tl::Path::Small;
     r->block = tl::kSmallBlock;
@@ -317,9 +324,22 @@ tl_status resolve(tl::KernelId k, const tl_tune* t, const Layout& lay, int64_t n
   return TL_OK;
 }
 
-tl_status run(tl::KernelId k, const Checker& c, const tl_tune* tune, const tl::KArgs& a,
-              void* stream) {
+// Bytes of the inputs a body reads for the outputs present.
+template <class Op>
+int64_t needed_bytes(const tl::KArgs& a, int64_t n) {
+  unsigned outs = 0;
+  for (int f = 0; f < Op::NF_OUT; ++f) outs |= a.out[f] != nullptr ? 1u << f : 0u;
+  int64_t comps = 0;
+  for (int f = 0; f < Op::NF_IN; ++f)
+    if (Op::needs(outs) >> f & 1u) comps += Op::fin[f];
+  return comps * n * 8;
+}
+
+tl_status run(tl::KernelId k, Checker& c, const tl_tune* tune, const tl::KArgs& a, void* stream) {
   tl::Resolved r;
+  if (c.lay.partial)
+    c.lay.in_bytes = k == tl::KernelId::ChainBwd ? needed_bytes<tl::OpChainBwd>(a, c.n)
+                                                 : needed_bytes<tl::OpChainFwdBwd>(a, c.n);
   tl_status s = resolve(k, tune, c.lay, c.n, &r);
   if (s != TL_OK) return s;
   hipError_t e = r.lanes > 1
@@ -761,6 +781,7 @@ struct PlanInput {
     lay.vec_ok = lay.vec_ok && c.lay.vec_ok;
     lay.buf_ok = lay.buf_ok && c.lay.buf_ok;
     lay.line_ok = lay.line_ok && c.lay.line_ok;
+    lay.partial = lay.partial || c.lay.partial;
     lay.in_bytes += c.lay.in_bytes;
     lay.out_bytes += c.lay.out_bytes;
     points += nd;

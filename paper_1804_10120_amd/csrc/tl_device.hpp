@@ -194,6 +194,15 @@ struct OpChainBwd {
   static constexpr int fout[NF_OUT] = {6, 18, 3, 9, 6, 1};
   static constexpr int NIN = 40, NOUT = 43;
 
+  // The inputs (bits g, dg, beta, K, alpha, w) to read for the given outputs
+  // (bits g_bar, dg_bar, beta_bar, dbeta_bar, K_bar, alpha_bar).  alpha and w
+  // always: alpha is one component, and the compiler forms -2 alpha inside a
+  // branch around its load, where it waits for every load before it.
+  static __host__ __device__ constexpr unsigned needs(unsigned outs) {
+    return ((outs & 7u) ? 1u : 0u) | ((outs & 5u) ? 2u : 0u) | ((outs & 3u) ? 4u : 0u) |
+           ((outs & 32u) ? 8u : 0u) | 48u;
+  }
+
   // Everything that does not need d g: b = g^-1 beta (kept as cofactors, 1/det
   // and b for phase2) and the gradients with respect to K, alpha, d beta and
   // d g, which depend on w, alpha, K and b only.
@@ -287,6 +296,13 @@ struct OpChainFwdBwd {
   static constexpr int fin[NF_IN] = {6, 18, 3, 9, 6, 1, 6};
   static constexpr int fout[NF_OUT] = {6, 6, 18, 3, 9, 6, 1};
   static constexpr int NIN = 49, NOUT = 49;
+
+  // d_t g (output 0) depends on everything but w; the gradients as in OpChainBwd.
+  static __host__ __device__ constexpr unsigned needs(unsigned outs) {
+    const unsigned b = OpChainBwd::needs(outs >> 1);
+    return ((outs & 1u) ? 63u : 0u) | (b & 7u) | (b & 56u) << 1;
+  }
+
   __device__ static inline void apply(const double* x, double* y) {
     OpChain::apply(x, y);
     double cof[6], r, b[3];

@@ -81,6 +81,21 @@ def test_chain_and_gradients(lay, want):
                                            tune=t), ncomps, lay)
 
 
+@pytest.mark.parametrize("lay", [(777, 0, 1), (2 ** 16 + 9, 3, 0)], ids=["small", "staged"])
+def test_every_subset_of_outputs(lay):
+    """The inputs read for each subset of the outputs are all that it depends on."""
+    need_gpu()
+    f = inputs(CHAIN + ("w",), lay, seed=4)
+    for bits in range(1, 128):
+        want = [bits >> k & 1 for k in range(7)]
+        ncomps = [c if w else 0 for c, w in zip((6, 6, 18, 3, 9, 6, 1), want)]
+        same(lambda o, t: tl_dtg_chain_fwd_bwd(*[f[k] for k in CHAIN], f["w"], o[0], o[1:],
+                                               want=want, tune=t), ncomps, lay)
+        if any(want[1:]):
+            same(lambda o, t: tl_dtg_chain_bwd(*[f[k] for k in BWD], *o, want=want[1:], tune=t),
+                 ncomps[1:], lay)
+
+
 @pytest.mark.parametrize("name", ["assign1", "add3", "mult2", "mult3", "contract1", "contract2",
                                   "contract3", "kij"])
 @pytest.mark.parametrize("lay", [LAYOUTS[1], LAYOUTS[2], LAYOUTS[6]], ids=[IDS[1], IDS[2], IDS[6]])
