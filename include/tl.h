@@ -228,26 +228,25 @@ tl_status tl_batch_plan_destroy(tl_batch_plan* plan);
  * tl_dtg_chain on every domain with the batched kernel of tl_batch_plan_create
  * -- the same launch, tile order and results as creating a plan with the same
  * doms and tune, calling tl_batch_plan_launch_direct and destroying the plan --
- * but with the plan's tables (domain descriptors, first tile of each domain,
- * tile -> domain map) in a fixed array of device memory that the library
- * holds on each device it runs on, from the first call there until the
- * process ends (about 1.4 MB).  Kernels launched on `stream` write the tables
- * from their kernel arguments, then the batched kernel runs; the call makes no
- * device allocation, no host-to-device copy and no memset, and returns once
- * the launches are queued (asynchronous).  Being kernel launches only, the
- * call may be captured into a HIP graph: each replay writes the tables again
- * before the batched kernel reads them.  The caller passes every input and
- * output, as for a plan; the domains' buffers must stay valid until the work
- * on `stream` has finished.
- * Every call on a device shares that device's array and leaves its tables in
- * it: calls that overlap on one device (on different streams, or from several
- * host threads without ordering between them) race and may read each other's
- * tables; order them on one stream.
+ * but without the plan's tables: with tune NULL the subgrids' descriptors travel
+ * in the kernel arguments, 46 subgrids a launch.  With a launch shape given (or
+ * a field of 4 GiB or more) kernels first write the tables from their arguments
+ * into a fixed array of device memory that the library holds on each device it
+ * runs on until the process ends (about 1.4 MB).  The call makes no device
+ * allocation, no host-to-device copy and no memset, and returns once the
+ * launches are queued (asynchronous).  Being kernel launches only, it may be
+ * captured into a HIP graph.  The caller passes every input and output, as for
+ * a plan; the domains' buffers must stay valid until the work on `stream` has
+ * finished.
+ * Calls that write the tables share the device's array and leave theirs in it:
+ * such calls race if they overlap on one device (on different streams, or from
+ * several host threads without ordering between them); order them on one
+ * stream.
  * Limits: 1 <= ndom <= TL_NOALLOC_MAX_DOMAINS, and at most TL_NOALLOC_MAX_TILES
  * tiles in all, a domain of n points taking ceil(n / (block * ppt)) tiles of
- * the resolved launch shape (the default, one block of 128 threads per tile,
- * allows 33.5 M points); beyond either limit TL_ERR_SIZE, before anything is
- * launched.  Validation otherwise as for tl_batch_plan_create. */
+ * the launch shape (with tune NULL ceil(n / 128), so 33.5 M points); beyond
+ * either limit TL_ERR_SIZE, before anything is launched.  Validation otherwise
+ * as for tl_batch_plan_create. */
 #define TL_NOALLOC_MAX_DOMAINS 1024
 #define TL_NOALLOC_MAX_TILES 262144
 tl_status tl_batch_run_noalloc(const tl_domain* doms, int32_t ndom, const tl_tune* tune,

@@ -192,7 +192,8 @@ tl::Resolved defaults(tl::KernelId k, int64_t n) {
   tl::Resolved r;
   r.nt = true;
   r.grid_mult = 0;
-  if (k == tl::KernelId::ChainBatched || k == tl::KernelId::ChainBwdBatched) {
+  if (k == tl::KernelId::ChainBatched || k == tl::KernelId::ChainBwdBatched ||
+      k == tl::KernelId::ChainBatchedOnce) {
     r.block = 128;
     r.ppt = 1;
     r.xcd = false;
@@ -257,14 +258,16 @@ tl::Resolved defaults(tl::KernelId k, int64_t n) {
 // over 127^3 613 / 628; with less in flight they do not (Gamma 243 / 240, the
 // three contractions over 97^3 276 / 275, assign3 over 127^3 172 / 166).
 void default_path(tl::KernelId k, const Layout& lay, int64_t n, tl::Resolved* r) {
-  const bool batched = k == tl::KernelId::ChainBatched || k == tl::KernelId::ChainBwdBatched;
+  const bool once = k == tl::KernelId::ChainBatchedOnce;
+  const bool batched =
+      k == tl::KernelId::ChainBatched || k == tl::KernelId::ChainBwdBatched || once;
   const int64_t p16 = int64_t(1) << 16, p19 = int64_t(1) << 19, p20 = int64_t(1) << 20;
   const int64_t in = lay.in_bytes >> 20, out = lay.out_bytes >> 20;  // MiB
-  if (!lay.buf_ok || (batched && n < p16)) return;
+  if (!lay.buf_ok || (batched && !once && n < p16)) return;
   const bool xcd = lay.line_ok && !batched && (n == p20 || n == 2 * p20);
   if (xcd && !lay.partial) return;
   r->ppt = 1;
-  if (n >= p20 || (n >= p16 && (batched || !lay.line_ok))) {
+  if (n >= p20 || once || (n >= p16 && (batched || !lay.line_ok))) {
     r->path = tl::Path::Staged;
     r->block = tl::kStageBlock;
     if (n >= (lay.line_ok ? p20 : p19) && lay.in_bytes + lay.out_bytes >= 32 * 8 * n)
@@ -945,15 +948,23 @@ tl_status tl_batch_run_noalloc(const tl_domain* doms, int32_t ndom, const tl_tun
   const tl_status s1 = chain_domains(doms, ndom, &in);
   if (s1 != TL_OK) return s1;
   PlanTables t;
-  const tl_status s2 = plan_tables(tl::KernelId::ChainBatched, in, tune, &t, false);
+  const tl_status s2 = plan_tables(tl::KernelId::ChainBatchedOnce, in, tune, &t, false);
   if (s2 != TL_OK) return s2;
-  if (t.ntiles > TL_NOALLOC_MAX_TILES)
+  const bool staged = t.r.path == tl::Path::Staged;
+  // The limit of a call without a launch shape counts tiles of 128 points,
+  // whichever kernel it runs.
+  const int per = staged ? 128 : t.r.block * t.r.ppt;
+  int64_t tiles = 0;
+  for (int64_t nd : in.n) tiles += (nd + per - 1) / per;
+  if (tiles > TL_NOALLOC_MAX_TILES)
     return fail(TL_ERR_SIZE,
                 "%lld tiles of %d points exceed TL_NOALLOC_MAX_TILES=%d (a larger block or ppt "
                 "takes fewer tiles; a batch plan has no such limit)",
-                (long long)t.ntiles, t.r.block * t.r.ppt, TL_NOALLOC_MAX_TILES);
-  hipError_t e = tl::launch_batched_noalloc(t.r, t.doms.data(), t.start.data(), ndom, t.ntiles,
-                                            t.grid, t.chunk, static_cast<hipStream_t>(stream));
+                (long long)tiles, per, TL_NOALLOC_MAX_TILES);
+  const hipStream_t hs = static_cast<hipStream_t>(stream);
+  hipError_t e = staged ? tl::launch_batched_args(t.r, t.doms.data(), ndom, hs)
+                        : tl::launch_batched_noalloc(t.r, t.doms.data(), t.start.data(), ndom,
+                                                     t.ntiles, t.grid, t.chunk, hs);
   if (e != hipSuccess) return hip_fail(e, "no-allocation batched launch");
   return TL_OK;
 }

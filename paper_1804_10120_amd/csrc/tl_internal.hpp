@@ -30,8 +30,9 @@ struct alignas(64) BatchDomain {
 // Generic: a body chosen by the caller (the benchmark expressions, the
 // bandwidth twins, generated kernels): the fused chain's default shapes, and
 // the points per lane settled by the body's stream count (op_ppt).
+// ChainBatchedOnce: the forward batch run without a plan.
 enum class KernelId { SymInverse, Christoffel, CovDeriv, Dtg, Chain, ChainBwd, ChainBatched,
-                      ChainFwdBwd, ChainBwdBatched, Generic };
+                      ChainFwdBwd, ChainBwdBatched, ChainBatchedOnce, Generic };
 
 // The staged kernel (tl_stream.hpp): its block, and the components it passes
 // through LDS at a time (2 buffers x 8 x 256 doubles, 32 KB).
@@ -110,6 +111,10 @@ hipError_t launch_batched(KernelId k, const Resolved& r, const BatchDomain* doms
 hipError_t launch_batched_noalloc(const Resolved& r, const BatchDomain* doms, const int64_t* start,
                                   int32_t ndom, int64_t ntiles, int64_t grid, int64_t chunk,
                                   hipStream_t s);
+// The same with the staged kernel, the descriptors of up to kArgDomains
+// subgrids at a time in its kernel argument and no table in device memory.
+hipError_t launch_batched_args(const Resolved& r, const BatchDomain* doms, int32_t ndom,
+                               hipStream_t s);
 hipError_t launch_copy(const double* src, double* dst, int64_t n, int64_t grid, hipStream_t s);
 hipError_t launch_read(const double* src, double* partial, int64_t n, int64_t grid, bool vec,
                        hipStream_t s);

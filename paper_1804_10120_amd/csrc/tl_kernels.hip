@@ -58,6 +58,50 @@ __global__ __launch_bounds__(kStageBlock) void k_batched_staged(
   tile_staged<Op, LD, ST>(buf, a, b, n, (t - start[d]) * kStageBlock);
 }
 
+// A batch run once, without tables in device memory: the descriptors of up to
+// kArgDomains subgrids come with the launch.  Only what the forward reads, in
+// 32-bit words (a field below 4 GiB has a leading dimension below 2^29):
+//   0..11 input pointers, 12..13 the output's, 14..18 leading dimensions of
+//   g, dg, beta, dbeta, K, 19 of d_t g, 20 n
+// so that 46 fit the 4 KB of kernel arguments that every HIP runtime accepts.
+// A block finds its subgrid by counting the first tiles at or before its own:
+// 46 scalar compares on values that every block of a compute unit reads from
+// the scalar cache.  Before, kernels of their own wrote tables from their
+// arguments and the batch then read them, 10 us of 25 for 48 small subgrids.
+constexpr int kArgDomains = 46;
+constexpr int kArgWords = 21;
+struct ArgBatch {
+  int32_t ntiles, order;
+  uint32_t start[kArgDomains];  // first tile of each; beyond the last, UINT32_MAX
+  uint32_t w[kArgDomains][kArgWords];
+};
+static_assert(sizeof(ArgBatch) <= 4096, "kernel argument too large");
+
+template <int LD, int ST>
+__global__ __launch_bounds__(kStageBlock) void k_batched_args(ArgBatch batch) {
+  __shared__ double buf[2][kStageComps][kStageBlock];
+  const int64_t t = ordered_tile(batch.order);
+  if (t >= batch.ntiles) return;
+  int d = -1;
+#pragma unroll
+  for (int j = 0; j < kArgDomains; ++j) d += batch.start[j] <= static_cast<uint32_t>(t) ? 1 : 0;
+  const uint32_t* w = batch.w[d];
+  const auto ptr = [&](int k) {
+    return static_cast<uintptr_t>(w[2 * k]) | static_cast<uintptr_t>(w[2 * k + 1]) << 32;
+  };
+  KArgs a;
+#pragma unroll
+  for (int f = 0; f < OpChain::NF_IN; ++f) {
+    a.in[f] = reinterpret_cast<const double*>(ptr(f));
+    a.ldin[f] = f < 5 ? w[14 + f] : 0;
+  }
+  a.out[0] = reinterpret_cast<double*>(ptr(6));
+  a.ldout[0] = w[19];
+  const int64_t n = w[20];
+  const Bufs<OpChain> b = make_bufs<OpChain>(a, n);
+  tile_staged<OpChain, LD, ST>(buf, a, b, n, (t - batch.start[d]) * kStageBlock);
+}
+
 __global__ void k_copy(const double* __restrict__ src, double* __restrict__ dst, int64_t n) {
   const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x * 2;
   for (int64_t i = (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) * 2; i < n;
@@ -262,6 +306,46 @@ hipError_t launch_batched(KernelId k, const Resolved& r, const BatchDomain* doms
   hipError_t e = hipLaunchKernel(fn, dim3(static_cast<unsigned>(grid)), dim3(r.block), args, 0, s);
   if (e != hipSuccess) return e;
   return hipGetLastError();
+}
+
+hipError_t launch_batched_args(const Resolved& r, const BatchDomain* doms, int32_t ndom,
+                               hipStream_t s) {
+#define TL_PTR(LD, ST) reinterpret_cast<const void*>(&k_batched_args<LD, ST>)
+  const void* fn = TL_BY_POLICY(r, TL_PTR);
+#undef TL_PTR
+  for (int32_t d0 = 0; d0 < ndom;) {
+    ArgBatch batch;
+    batch.order = r.order;
+    int used = 0;
+    int64_t tiles = 0;
+    for (; d0 < ndom && used < kArgDomains; ++d0) {
+      const BatchDomain& x = doms[d0];
+      if (x.n == 0) continue;
+      batch.start[used] = static_cast<uint32_t>(tiles);
+      uint32_t* w = batch.w[used++];
+      const auto put = [&](int k, const void* p) {
+        const uintptr_t v = reinterpret_cast<uintptr_t>(p);
+        w[2 * k] = static_cast<uint32_t>(v);
+        w[2 * k + 1] = static_cast<uint32_t>(v >> 32);
+      };
+      for (int f = 0; f < 6; ++f) put(f, x.args.in[f]);
+      put(6, x.args.out[0]);
+      for (int f = 0; f < 5; ++f) w[14 + f] = static_cast<uint32_t>(x.args.ldin[f]);
+      w[19] = static_cast<uint32_t>(x.args.ldout[0]);
+      w[20] = static_cast<uint32_t>(x.n);
+      tiles += (x.n + kStageBlock - 1) / kStageBlock;
+    }
+    if (used == 0) break;
+    for (int j = used; j < kArgDomains; ++j) batch.start[j] = UINT32_MAX;
+    batch.ntiles = static_cast<int32_t>(tiles);
+    void* args[] = {&batch};
+    hipError_t e = hipLaunchKernel(fn, dim3(static_cast<unsigned>(ordered_grid(tiles, r.order))),
+                                   dim3(kStageBlock), args, r.lds_pad, s);
+    if (e != hipSuccess) return e;
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_copy(const double* src, double* dst, int64_t n, int64_t grid, hipStream_t s) {

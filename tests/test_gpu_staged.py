@@ -8,7 +8,7 @@ import pytest
 import torch
 
 from gpu_util import CANARY, need_gpu
-from paper_1804_10120_amd import (BatchPlan, generated, tl_christoffel, tl_cov_deriv, tl_dtg,
+from paper_1804_10120_amd import (BatchPlan, generated, tl_batch_run_noalloc, tl_christoffel, tl_cov_deriv, tl_dtg,
                                   tl_dtg_chain, tl_dtg_chain_bwd, tl_dtg_chain_fwd_bwd, tl_expr,
                                   tl_sym_inverse)
 
@@ -143,3 +143,19 @@ def test_batch(kind, pad):
         got.append([b for m in made for _, b in m.values()])
     for k, (a, b) in enumerate(zip(*got)):
         assert torch.equal(a, b), f"field {k}: {int((a != b).sum())} of {a.numel()} differ"
+
+
+@pytest.mark.parametrize("count", [1, 45, 46, 47, 93])
+@pytest.mark.parametrize("pad", [0, None], ids=["contiguous", "lines"])
+def test_batch_without_plan(count, pad):
+    """Descriptors in the kernel arguments, 46 subgrids a launch, empty subgrids between them."""
+    need_gpu()
+    sizes = [0 if i % 5 == 3 else 1 + (i * 337) % 900 for i in range(count)]
+    doms = [inputs(CHAIN, (n, pad, 0), seed=40 + i) for i, n in enumerate(sizes)]
+    got = []
+    for tune in (None, dict(block=128, ppt=1, nt=True)):
+        made = [field(6, (n, pad, 0)) for n in sizes]
+        tl_batch_run_noalloc([dict(d, dtg=v) for d, (v, _) in zip(doms, made)], tune=tune)
+        torch.cuda.synchronize()
+        got.append([b for _, b in made])
+    assert all(torch.equal(a, b) for a, b in zip(*got))
