@@ -210,9 +210,10 @@ typedef struct {
 tl_status tl_batch_plan_bwd_create(const tl_domain_bwd* doms, int32_t ndom, const tl_tune* tune,
                                    tl_batch_plan** out);
 
-/* Replays the captured launch on `stream` (asynchronous). */
+/* Runs the plan's launch on `stream` (asynchronous): the kernel itself, or the
+ * captured graph if the stream is being captured. */
 tl_status tl_batch_plan_launch(tl_batch_plan* plan, void* stream);
-/* Launches the same kernel directly, without the graph (asynchronous). */
+/* Launches the same kernel, never the graph (asynchronous). */
 tl_status tl_batch_plan_launch_direct(tl_batch_plan* plan, void* stream);
 /* Total points, tiles and grid size of a plan (any pointer may be NULL). */
 tl_status tl_batch_plan_info(const tl_batch_plan* plan, int64_t* points, int64_t* tiles,

@@ -1001,11 +1001,26 @@ static tl_status plan_device_check(const tl_batch_plan* p) {
   return TL_OK;
 }
 
+static tl_status plan_launch_kernel(const tl_batch_plan* p, hipStream_t s) {
+  hipError_t e = tl::launch_batched(p->kid, p->r, p->d_doms, p->d_start, p->d_tile_dom, p->ntiles,
+                                    p->grid, p->chunk, s);
+  if (e != hipSuccess) return hip_fail(e, "batched launch");
+  return TL_OK;
+}
+
+// The plan's graph holds one kernel node, and launching that kernel costs less
+// than replaying the graph: 6.2 us a call on the host against 18.3 (8 subgrids
+// of 8^3 to 12^3 points), 652 against 656 us over 256 subgrids.  The graph serves
+// a stream that is being captured.
 tl_status tl_batch_plan_launch(tl_batch_plan* p, void* stream) {
   if (p == nullptr) return fail(TL_ERR_NULL, "plan is NULL");
   if (plan_device_check(p) != TL_OK) return TL_ERR_INVALID;
   if (p->ntiles == 0) return TL_OK;
-  hipError_t e = hipGraphLaunch(p->exec, static_cast<hipStream_t>(stream));
+  const hipStream_t s = static_cast<hipStream_t>(stream);
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone)
+    return plan_launch_kernel(p, s);
+  hipError_t e = hipGraphLaunch(p->exec, s);
   if (e != hipSuccess) return hip_fail(e, "hipGraphLaunch");
   return TL_OK;
 }
@@ -1014,10 +1029,7 @@ tl_status tl_batch_plan_launch_direct(tl_batch_plan* p, void* stream) {
   if (p == nullptr) return fail(TL_ERR_NULL, "plan is NULL");
   if (plan_device_check(p) != TL_OK) return TL_ERR_INVALID;
   if (p->ntiles == 0) return TL_OK;
-  hipError_t e = tl::launch_batched(p->kid, p->r, p->d_doms, p->d_start, p->d_tile_dom,
-                                    p->ntiles, p->grid, p->chunk, static_cast<hipStream_t>(stream));
-  if (e != hipSuccess) return hip_fail(e, "batched launch");
-  return TL_OK;
+  return plan_launch_kernel(p, static_cast<hipStream_t>(stream));
 }
 
 tl_status tl_batch_plan_info(const tl_batch_plan* p, int64_t* points, int64_t* tiles,

@@ -571,12 +571,12 @@ class BatchPlan:
         return [tuple(d[k + "_bar"] for k in GRAD_NAMES) for d in self.domains]
 
     def run(self, stream=None):
-        """Replay the captured graph on ``stream`` (default: current stream)."""
+        """Run the plan's launch on ``stream`` (default: current stream)."""
         with torch.cuda.device(self.device):
             check(lib().tl_batch_plan_launch(self._plan, _stream(self.device, stream)))
 
     def run_direct(self, stream=None):
-        """Launch the persistent kernel directly (no graph)."""
+        """Launch the plan's kernel, never its graph."""
         with torch.cuda.device(self.device):
             check(lib().tl_batch_plan_launch_direct(self._plan, _stream(self.device, stream)))
 
