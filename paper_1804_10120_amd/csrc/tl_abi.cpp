@@ -249,9 +249,11 @@ tl::Resolved defaults(tl::KernelId k, int64_t n) {
 //  - outputs are left in the cache beside them only up to 32 MiB in all (at
 //    62 MB Gamma takes 10.3 us against 10.7 with three sets, 14.9 against 10.7
 //    with six);
-//  - with inputs beyond 96 MiB, outputs of at most 64 MiB are kept (the forward
-//    over 112^3 points 96 us against 101, d_t g over 97^3 26.7 / 29.4), for the
-//    next kernel to find.
+//  - with inputs beyond 96 MiB, outputs of less than 96 MiB are kept for the next
+//    kernel to find (Gamma over 84^3 points 34.0 us against 42.3 streamed, the
+//    covariant derivative over 100^3 49.3 / 52.1, d_t g over 97^3 26.7 / 29.4;
+//    with six sets within 2 %); staged ones only below 64 MiB (the forward over
+//    112^3 93 / 98, but over 127^3 ragged points 150 / 146).
 // Ragged tiles share lines with their neighbours on the same XCD, and where a
 // body writes about as much as it reads and moves a lot, loads left in the L2
 // pay: the adjoint over 159^3 points 504 us against 534, the three contractions
@@ -278,7 +280,7 @@ void default_path(tl::KernelId k, const Layout& lay, int64_t n, tl::Resolved* r)
     r->block = tl::kSmallBlock;
   }
   r->keep_in = in < 96 || (!lay.line_ok && in >= 512 && 4 * out >= 3 * in);
-  r->keep_out = in + out < 32 || (in >= 96 && out < 64);
+  r->keep_out = in + out < 32 || (in >= 96 && out < (r->path == tl::Path::Small ? 96 : 64));
 }
 
 tl_status resolve(tl::KernelId k, const tl_tune* t, const Layout& lay, int64_t n,
