@@ -10,6 +10,7 @@ import os
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(PKG, "libtl.so")
+BIND_PATH = os.path.join(PKG, "_bind.so")
 
 TL_OK, TL_ERR_NULL, TL_ERR_SIZE, TL_ERR_ALIAS, TL_ERR_ALIGN, TL_ERR_HIP, TL_ERR_INVALID = range(7)
 TL_TUNE_NT = 1
@@ -121,6 +122,36 @@ def lib():
             raise RuntimeError(f"libtl.so ABI version {v}, expected {ABI_VERSION}")
         _lib = L
     return _lib
+
+
+# the entry points the extension calls, in the order of its table
+BOUND = ("tl_sym_inverse", "tl_christoffel", "tl_cov_deriv", "tl_dtg", "tl_dtg_chain",
+         "tl_dtg_chain_bwd", "tl_dtg_chain_fwd_bwd", "tl_expr", "tl_batch_run_noalloc",
+         "tl_batch_plan_launch")
+INVERSE, CHRISTOFFEL, COV_DERIV, DTG, CHAIN, CHAIN_BWD, CHAIN_FWD_BWD = range(7)
+
+_bind = None
+
+
+def address(fn):
+    """The address of a ctypes function."""
+    return ctypes.cast(fn, ctypes.c_void_p).value
+
+
+def bind():
+    """The extension that marshals plain calls natively (csrc/py_bind.cpp), bound
+    to the loaded library; raises if it has not been built."""
+    global _bind
+    if _bind is None:
+        L = lib()
+        if not os.path.exists(BIND_PATH):
+            raise RuntimeError(
+                f"{BIND_PATH} is missing: build it with `python -m paper_1804_10120_amd.build` "
+                "(there is no fallback implementation)")
+        from . import _bind as m
+        m.init(tuple(address(getattr(L, name)) for name in BOUND), check)
+        _bind = m
+    return _bind
 
 
 def check(status):

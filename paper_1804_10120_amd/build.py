@@ -1,4 +1,5 @@
-"""Builds ``libtl.so`` (the C-ABI library of HIP kernels) for gfx950 in-tree.
+"""Builds ``libtl.so`` (the C-ABI library of HIP kernels) for gfx950 in-tree, and
+``_bind.so``, the torch binding's extension.
 
     python -m paper_1804_10120_amd.build
 
@@ -20,6 +21,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libtl.so")
+BIND = os.path.join(PKG, "_bind.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 SOURCES = ["tl_kernels.hip", "tl_noalloc.hip", "tl_expr.hip", "generated/tlg_kernels.hip",
@@ -38,6 +40,30 @@ def _compile(src, verbose):
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)
     return src, obj, r
+
+
+def _compile_bind(verbose):
+    """The torch binding's extension (csrc/py_bind.cpp): host code only."""
+    import sysconfig
+
+    import torch
+    t = os.path.dirname(torch.__file__)
+    tmp = BIND + ".tmp"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-isystem", os.path.join(t, "include"),
+           "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+           "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "py_bind.cpp"), "-o", tmp, "-L", os.path.join(t, "lib"),
+           "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        sys.stderr.write(r.stderr)
+        raise RuntimeError("the torch binding's extension did not compile")
+    os.replace(tmp, BIND)
 
 
 _REMARK = re.compile(r"remark: +(Function Name|TotalSGPRs|VGPRs|AGPRs|ScratchSize \[bytes/lane\]|"
@@ -107,8 +133,10 @@ def build(verbose: bool = False) -> str:
     from .codegen.__main__ import main as codegen
     codegen([])
     os.makedirs(BUILD, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as pool:
+    with ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as pool:
+        bind = pool.submit(_compile_bind, verbose)
         results = list(pool.map(lambda s: _compile(s, verbose), SOURCES))
+        bind.result()
     objs, report = [], []
     for src, obj, r in results:
         report.append(r.stderr)

@@ -13,12 +13,13 @@ import os
 
 import torch
 
-from . import ops
+from . import _abi, ops
 from ._abi import CField, Field, Tune, check, lib
 
 MANIFEST = os.path.join(os.path.dirname(os.path.abspath(__file__)), "generated.json")
 _programs = None
 _fns = {}
+_plain = {}     # name -> (address, component counts of inputs and outputs, and the input count)
 
 
 def programs():
@@ -41,10 +42,28 @@ def _fn(name):
     return _fns[name]
 
 
+def _call_plain(name, inputs, outs):
+    """The call made natively (csrc/py_bind.cpp), or None if it is not a plain one."""
+    if name not in _plain:
+        p = programs()[name]
+        comps = [t["ncomp"] for t in p["inputs"]], [t["ncomp"] for t in p["outputs"]]
+        _plain[name] = (_abi.address(_fn(name)), bytes((*comps[0], *comps[1], len(comps[0]))))
+    address, comps = _plain[name]
+    nout = len(comps) - 1 - comps[-1]
+    outs = (None,) * nout if outs is None else outs
+    if len(inputs) != comps[-1] or len(outs) != nout:
+        return None
+    return _abi.bind().fields(address, comps, *inputs, *outs)
+
+
 def call(name, *inputs, outs=None, stream=None, tune=None):
     """Runs generated program ``name``; returns the tuple of output fields.
     Output components that the program does not write are left untouched (so
     pass ``outs`` when they matter)."""
+    if stream is None and tune is None and ops._recording() is None:
+        r = _call_plain(name, inputs, outs)
+        if r is not None:
+            return r
     p = programs()[name]
     if len(inputs) != len(p["inputs"]):
         raise ValueError(f"{name}: expected inputs {[t['name'] for t in p['inputs']]}")

@@ -184,6 +184,14 @@ class record:
         return False
 
 
+def _plain(entry, want, stream, tune, *fields):
+    """The call made natively (csrc/py_bind.cpp): its output or outputs, or None if
+    it is not a plain one (the caller then goes through the checks below)."""
+    if stream is not None or tune is not None or _recording() is not None:
+        return None
+    return _abi.bind().call(entry, want, *fields)
+
+
 def _auto(tune, kernel, n):
     """tune="auto": the autotuner's cached shape for (kernel, size class), or
     the library default when nothing is cached."""
@@ -207,6 +215,9 @@ def _run(fn, c, *args, stream=None, tune=None, kernel=None):
 
 def tl_sym_inverse(g, ginv=None, *, stream=None, tune=None):
     """g^ij = inverse of the symmetric g_ij: [6,n] -> [6,n]."""
+    r = _plain(_abi.INVERSE, 1, stream, tune, g, ginv)
+    if r is not None:
+        return r
     c = _Call()
     c.add(g, "g")
     ginv = c.out(ginv, "ginv", g)
@@ -217,6 +228,9 @@ def tl_sym_inverse(g, ginv=None, *, stream=None, tune=None):
 
 def tl_christoffel(ginv, dg, gamma=None, *, stream=None, tune=None):
     """Gamma^i_jk from g^ij [6,n] and d_k g_ij [18,n] -> [18,n]."""
+    r = _plain(_abi.CHRISTOFFEL, 1, stream, tune, ginv, dg, gamma)
+    if r is not None:
+        return r
     c = _Call()
     c.add(ginv, "ginv")
     c.add(dg, "dg")
@@ -229,6 +243,9 @@ def tl_christoffel(ginv, dg, gamma=None, *, stream=None, tune=None):
 
 def tl_cov_deriv(gamma, beta, dbeta, nabla_beta=None, *, stream=None, tune=None):
     """nabla_j beta_i from Gamma [18,n], beta_i [3,n], d_j beta_i [9,n] -> [9,n]."""
+    r = _plain(_abi.COV_DERIV, 1, stream, tune, gamma, beta, dbeta, nabla_beta)
+    if r is not None:
+        return r
     c = _Call()
     c.add(gamma, "gamma")
     c.add(beta, "beta")
@@ -242,6 +259,9 @@ def tl_cov_deriv(gamma, beta, dbeta, nabla_beta=None, *, stream=None, tune=None)
 
 def tl_dtg(alpha, K, nabla_beta, dtg=None, *, stream=None, tune=None):
     """d_t g_ij from alpha [n], K_ij [6,n], nabla_j beta_i [9,n] -> [6,n]."""
+    r = _plain(_abi.DTG, 1, stream, tune, alpha, K, nabla_beta, dtg)
+    if r is not None:
+        return r
     c = _Call()
     c.add(alpha, "alpha")
     c.add(K, "K")
@@ -255,6 +275,9 @@ def tl_dtg(alpha, K, nabla_beta, dtg=None, *, stream=None, tune=None):
 
 def tl_dtg_chain(g, dg, beta, dbeta, K, alpha, dtg=None, *, stream=None, tune=None):
     """Fused d_t g_ij from g, d g, beta, d beta, K, alpha -> [6,n]."""
+    r = _plain(_abi.CHAIN, 1, stream, tune, g, dg, beta, dbeta, K, alpha, dtg)
+    if r is not None:
+        return r
     c = _Call()
     for t, name in ((g, "g"), (dg, "dg"), (beta, "beta"), (dbeta, "dbeta"), (K, "K"),
                     (alpha, "alpha")):
@@ -264,6 +287,11 @@ def tl_dtg_chain(g, dg, beta, dbeta, K, alpha, dtg=None, *, stream=None, tune=No
          _cf(alpha, 1), _f(dtg, 6), stream=stream, tune=tune,
          kernel="dtg_chain")
     return dtg
+
+
+def _mask(want, n):
+    """``want`` as bits, all set for None."""
+    return (1 << n) - 1 if want is None else sum(1 << k for k in range(n) if want[k])
 
 
 GRAD_NAMES = ("g", "dg", "beta", "dbeta", "K", "alpha")
@@ -278,6 +306,11 @@ def tl_dtg_chain_bwd(g, dg, beta, K, alpha, w, g_bar=None, dg_bar=None, beta_bar
     ``want`` is a 6-tuple of booleans in that order; an unwanted gradient is
     neither computed into memory nor allocated and comes back as None.
     """
+    if want is None or len(want) == 6:
+        r = _plain(_abi.CHAIN_BWD, _mask(want, 6), stream, tune, g, dg, beta, K, alpha, w,
+                   g_bar, dg_bar, beta_bar, dbeta_bar, K_bar, alpha_bar)
+        if r is not None:
+            return r
     c = _Call()
     for t, name in ((g, "g"), (dg, "dg"), (beta, "beta"), (K, "K"), (alpha, "alpha"), (w, "w")):
         c.add(t, name)
@@ -309,6 +342,11 @@ def tl_dtg_chain_fwd_bwd(g, dg, beta, dbeta, K, alpha, w, dtg=None, grads=None, 
     allocated when wanted); ``want`` is a 7-tuple of booleans for d_t g and the
     six gradients; an unwanted output is not written and comes back as None.
     """
+    if (want is None or len(want) == 7) and (grads is None or len(grads) == 6):
+        r = _plain(_abi.CHAIN_FWD_BWD, _mask(want, 7), stream, tune, g, dg, beta, dbeta, K, alpha,
+                   w, dtg, *(grads if grads is not None else (None,) * 6))
+        if r is not None:
+            return r[0], r[1:]
     c = _Call()
     for t, name in ((g, "g"), (dg, "dg"), (beta, "beta"), (dbeta, "dbeta"), (K, "K"),
                     (alpha, "alpha"), (w, "w")):
@@ -417,10 +455,22 @@ def tl_expr_shape(expr):
     return tuple(ic[:nin.value]), oc.value
 
 
+_expr_comps = {}    # id -> component counts of the inputs, of the output, and the input count
+
+
 def tl_expr(expr, *inputs, out=None, stream=None, tune=None):
     """A Sec. 5.1 benchmark expression over [C, n] device fields given in the
     order of its right-hand side; returns (or fills) the left-hand side."""
     eid = _abi.EXPRS.index(expr) if isinstance(expr, str) else int(expr)
+    if stream is None and tune is None and _recording() is None:
+        comps = _expr_comps.get(eid)
+        if comps is None:
+            ic, oc = tl_expr_shape(eid)
+            comps = _expr_comps[eid] = bytes((*ic, oc, len(ic)))
+        if len(inputs) == comps[-1]:
+            r = _abi.bind().fields(-1 - eid, comps, *inputs, out)
+            if r is not None:
+                return r[0]
     ic, oc = tl_expr_shape(eid)
     if len(inputs) != len(ic):
         raise ValueError(f"{_abi.EXPRS[eid]}: expected {len(ic)} inputs, got {len(inputs)}")
@@ -464,6 +514,10 @@ def tl_batch_run_noalloc(domains, *, stream=None, tune=None):
     overlap on one device race (they share the array); order them on one
     stream.
     """
+    if stream is None and tune is None and _recording() is None:
+        r = _abi.bind().noalloc(domains)
+        if r is not None:
+            return r
     arr = (Domain * len(domains))()
     device = None
     for i, d in enumerate(domains):
@@ -572,6 +626,9 @@ class BatchPlan:
 
     def run(self, stream=None):
         """Run the plan's launch on ``stream`` (default: current stream)."""
+        if stream is None and self._plan is not None:
+            if _abi.bind().plan_launch(self._plan.value, self.device.index):
+                return
         with torch.cuda.device(self.device):
             check(lib().tl_batch_plan_launch(self._plan, _stream(self.device, stream)))
 
