@@ -235,7 +235,11 @@ tl::Resolved defaults(tl::KernelId k, int64_t n) {
 // only for bodies of at least 32 component streams: with 12 the few loads in
 // flight no longer cover their latency (the inverse over 159^3 82 us against
 // 64), with 39 the covariant derivative takes 206 against 217.  Ragged grids
-// gain from it from 2^19 points on (the adjoint over 79^3 66.6 / 68.6 us).
+// gain from it from 2^19 points on (the adjoint over 87^3 85 / 87 us), but not
+// those below 2^20 whose outputs are kept in the cache and a quarter of the
+// inputs or more (the covariant derivative over 97^3 55.3 padded, 53.5 without;
+// the gauge part of the adjoint 70 / 69; the forward, with few outputs, over
+// 101^3 72.9 / 74.1).
 // Tile order: runs of 4 tiles per XCD where tiles share lines (at 159^3 points
 // the adjoint takes 549, 534, 534 and 528 us in plain order and in runs of 4,
 // 8 and 16, Gamma 241, 240, 243 and 241 us); else plain order, which at 160^3
@@ -253,7 +257,10 @@ tl::Resolved defaults(tl::KernelId k, int64_t n) {
 //    kernel to find (Gamma over 84^3 points 34.0 us against 42.3 streamed, the
 //    covariant derivative over 100^3 49.3 / 52.1, d_t g over 97^3 26.7 / 29.4;
 //    with six sets within 2 %); staged ones only below 64 MiB (the forward over
-//    112^3 93 / 98, but over 127^3 ragged points 150 / 146).
+//    112^3 93 / 98, but over 127^3 ragged points 150 / 146), unless fewer than 64
+//    streams of less than 2^20 points are in flight (the gauge part of the adjoint
+//    over 97^3 points, 50 streams, 69 kept and 74.5 streamed, over 89^3 54 / 58,
+//    Gamma over 85^3 37 / 43; the whole adjoint, 83 streams, over 81^3 76 / 70).
 // Ragged tiles share lines with their neighbours on the same XCD, and where a
 // body writes about as much as it reads and moves a lot, loads left in the L2
 // pay: the adjoint over 159^3 points 504 us against 534, the three contractions
@@ -269,18 +276,21 @@ void default_path(tl::KernelId k, const Layout& lay, int64_t n, tl::Resolved* r)
   const bool xcd = lay.line_ok && !batched && (n == p20 || n == 2 * p20);
   if (xcd && !lay.partial) return;
   r->ppt = 1;
+  const auto streams = [&](int64_t of) { return lay.in_bytes + lay.out_bytes >= of * 8 * n; };
   if (n >= p20 || once || (n >= p16 && (batched || !lay.line_ok))) {
     r->path = tl::Path::Staged;
     r->block = tl::kStageBlock;
-    if (n >= (lay.line_ok ? p20 : p19) && lay.in_bytes + lay.out_bytes >= 32 * 8 * n)
-      r->lds_pad = 24 << 10;
     r->order = xcd ? tl::kOrderXcd : lay.line_ok ? 0 : 4;
   } else {
     r->path = tl::Path::Small;
     r->block = tl::kSmallBlock;
   }
   r->keep_in = in < 96 || (!lay.line_ok && in >= 512 && 4 * out >= 3 * in);
-  r->keep_out = in + out < 32 || (in >= 96 && out < (r->path == tl::Path::Small ? 96 : 64));
+  const bool wide = r->path == tl::Path::Small || (n < p20 && !streams(64));
+  r->keep_out = in + out < 32 || (in >= 96 && out < (wide ? 96 : 64));
+  if (r->path == tl::Path::Staged && n >= (lay.line_ok ? p20 : p19) && streams(32) &&
+      !(n < p20 && r->keep_out && 4 * out >= in))
+    r->lds_pad = 24 << 10;
 }
 
 tl_status resolve(tl::KernelId k, const tl_tune* t, const Layout& lay, int64_t n,
