@@ -230,7 +230,10 @@ tl::Resolved defaults(tl::KernelId k, int64_t n) {
 // 117 us against 120 staged in that order, the forward 134 / 135), unless
 // outputs are left out: only the default kernels skip the inputs of those.  Otherwise
 // one point per lane in blocks of 64, stored from registers, which at 33^3 to
-// 80^3 is the fastest or within 2 % of it.
+// 80^3 is the fastest or within 2 % of it; up to 2^16 points, one wave for each
+// SIMD of the chip, with a streaming body's inputs loaded first (one contraction
+// over 40^3 13.4 us against 14.8, over 52^3 34 / 29), if ragged up to 2^15 (the
+// three contractions over 31^3 10.8 / 10.6, over 37^3 18.8 / 16.2).
 // Two blocks per compute unit (24 KB of LDS reserved beside the kernel's 32)
 // only for bodies of at least 32 component streams: with 12 the few loads in
 // flight no longer cover their latency (the inverse over 159^3 82 us against
@@ -284,6 +287,7 @@ void default_path(tl::KernelId k, const Layout& lay, int64_t n, tl::Resolved* r)
   } else {
     r->path = tl::Path::Small;
     r->block = tl::kSmallBlock;
+    r->preload = n <= (lay.line_ok ? p16 : p16 / 2);
   }
   r->keep_in = in < 96 || (!lay.line_ok && in >= 512 && 4 * out >= 3 * in);
   const bool wide = r->path == tl::Path::Small || (n < p20 && !streams(64));

@@ -58,8 +58,8 @@ struct Resolved {
   // of the default kernels: inputs and outputs left in the caches; of the
   // staged one: the tile order (ordered_tile of tl_stream.hpp), and the LDS
   // reserved beyond the kernel's own, which holds the blocks per compute unit
-  // down
-  bool keep_in = false, keep_out = false;
+  // down; of the small one: a streaming body loads all its inputs first
+  bool keep_in = false, keep_out = false, preload = false;
   int32_t order = 0;
   uint32_t lds_pad = 0;
 };

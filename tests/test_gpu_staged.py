@@ -109,6 +109,15 @@ def test_expressions(name, lay):
     same(lambda o, t: generated.call(name, *x, outs=o, tune=t), [nout], lay)
 
 
+@pytest.mark.parametrize("name", ["mult3", "contract1", "contract2", "contract3"])
+@pytest.mark.parametrize("lay", [(1, 0, 0), (65, 0, 3), (2 ** 15, 1, 0), (2 ** 15 + 1, 0, 0), (2 ** 16, None, 0),
+                                 (2 ** 16 + 1, None, 0)],
+                         ids=["n1", "n65", "n32768pad1", "n32769", "n65536lines", "n65537lines"])
+def test_small_expressions(name, lay):
+    """Up to 2^16 points (2^15 if ragged) a streaming body loads all its inputs first."""
+    test_expressions(name, lay)
+
+
 @pytest.mark.parametrize("name", ["spacetime_split", "lst_fixed_offset", "dtg_chain_invg"])
 def test_generated_several_fields(name):
     """Two output fields, an output with components that are never written, and many inputs."""
