@@ -67,8 +67,9 @@ typedef enum {
 typedef struct { const double* ptr; int64_t ld; } tl_cfield;
 typedef struct { double* ptr; int64_t ld; } tl_field;
 
-/* Launch tuning.  A NULL tl_tune* selects the measured default shape, which
- * depends on the kernel and on n.  In a supplied tl_tune a zero block, ppt or
+/* Launch tuning.  A NULL tl_tune* selects the measured default: the kernel, its
+ * launch and its cache policies by the kernel's streams, n and the alignment.
+ * In a supplied tl_tune a zero block, ppt or
  * grid_mult selects the default value of that member; flags are taken as
  * given.
  *   block      threads per block: 64, 128, 256, 512 or 1024
@@ -183,7 +184,7 @@ typedef struct {
 typedef struct tl_batch_plan tl_batch_plan;
 
 /* Builds a plan that evaluates tl_dtg_chain on every domain with one kernel
- * launch over the tiles of all domains, captured once into a HIP graph (by
+ * launch over the tiles of all domains, also captured once into a HIP graph (by
  * default one block per tile; tune->grid_mult > 0 makes it persistent, each
  * block walking a contiguous chunk of tiles).  The plan copies the domain
  * table and its tile tables to device memory (its only device allocations,
@@ -338,7 +339,8 @@ typedef struct {
  * "cov_deriv", "dtg", "dtg_chain", "dtg_chain_bwd", "dtg_chain_fwd_bwd",
  * "dtg_chain_batched", "dtg_chain_bwd_batched", or an expression name
  * "assign1" ... "contract3", "kij") would run with `tune` on a large grid
- * (ppt assumes aligned fields).  VGPRs and scratch come from the HIP runtime,
+ * (ppt assumes aligned fields; a NULL tune is answered for the default members
+ * given as a shape, the kernel that stores from registers).  VGPRs and scratch come from the HIP runtime,
  * SGPRs, AGPRs and the register-bound occupancy from the compiler's resource
  * report, compiled into the library when it was built, waves_per_simd from
  * the runtime's occupancy calculator; a value that cannot be obtained is -1.

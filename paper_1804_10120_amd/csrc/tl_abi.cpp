@@ -171,7 +171,9 @@ int num_cus() {
   return cu;
 }
 
-// Default launch shapes, measured on MI355X with the library's autotuner.
+// Default members of a launch shape (k_points), measured on MI355X with the
+// library's autotuner: what a given tl_tune leaves at zero, and the whole shape
+// where default_path below takes no kernel of its own.
 // Every kernel streams, so one rule serves nearly all of them: non-temporal
 // loads and stores always; for large grids one point per lane in blocks of 256,
 // with XCD-contiguous tiles when every XCD's share of each component is 1 or

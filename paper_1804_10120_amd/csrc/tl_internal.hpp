@@ -28,7 +28,7 @@ struct alignas(64) BatchDomain {
 };
 
 // Generic: a body chosen by the caller (the benchmark expressions, the
-// bandwidth twins, generated kernels): the fused chain's default shapes, and
+// bandwidth twins, generated kernels): the fused chain's launch shapes, and
 // the points per lane settled by the body's stream count (op_ppt).
 // ChainBatchedOnce: the forward batch run without a plan.
 enum class KernelId { SymInverse, Christoffel, CovDeriv, Dtg, Chain, ChainBwd, ChainBatched,

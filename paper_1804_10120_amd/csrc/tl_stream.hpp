@@ -4,12 +4,14 @@
 // One lane owns PPT consecutive grid points.  It issues every load of its
 // points up front -- one coalesced stream per tensor component, 16-byte
 // vector loads when PPT is 2 or 4 -- runs the per-point body (tl_device.hpp,
-// tl_expr_ops.hpp) in registers and streams the results out.  No LDS and no
-// MFMA: every point is independent and the contractions are 3 long, so the
-// kernels are bound by HBM bandwidth, and the levers are the bytes in flight
-// per CU (PPT, block size, occupancy), the cache policy (non-temporal loads and
-// stores), the order in which tiles meet the memory system (XCD order) and
-// the instructions spent on addresses (buffer addressing, below).
+// tl_expr_ops.hpp) in registers and streams the results out.  No MFMA: every
+// point is independent and the contractions are 3 long, so the kernels are
+// bound by HBM bandwidth, and the levers are the bytes in flight per CU (PPT,
+// block size, occupancy), the cache policy, the order in which tiles meet the
+// memory system (XCD order), the instructions spent on addresses (buffer
+// addressing, below) and whole lines stored at once (the staged kernel, which
+// passes outputs through LDS for that).  k_points runs the launch shapes that a
+// caller gives, k_small and k_staged the calls that give none.
 //
 // A body with more outputs than registers comfortably hold (kStream) is
 // instead given a loader ld(field, component) and a storer st(k, field,

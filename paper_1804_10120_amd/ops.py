@@ -547,7 +547,7 @@ def tl_batch_run_noalloc(domains, *, stream=None, tune=None):
 
 class BatchPlan:
     """tl_batch_plan_*: d_t g (kind="fwd") or its adjoint (kind="bwd") over
-    many subgrids in one graph-captured launch.
+    many subgrids in one launch (a graph node while a stream is captured).
 
     kind="fwd": ``domains`` is a sequence of dicts with the tensors g, dg,
     beta, dbeta, K, alpha and (optionally) dtg of one subgrid each.
