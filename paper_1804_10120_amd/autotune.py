@@ -2,8 +2,8 @@
 
 The paper picks a block size per kernel from a fixed rule tuned for its GPUs;
 here the shape is measured instead.  ``tune(kernel, n)`` times every candidate
-(block size, points per thread, non-temporal hint, persistent grid multiple)
-on seeded synthetic fields of ``n`` points with HIP events, rotating over
+(the library's default, which no shape describes, then block size, points per
+thread, non-temporal hint, persistent grid multiple) on seeded synthetic fields of ``n`` points with HIP events, rotating over
 enough buffer sets that the working set exceeds the last-level cache, and
 returns the fastest.  Results are cached as JSON keyed by kernel, GPU
 architecture and size class (``TLMI_TUNE_CACHE`` overrides the file).
@@ -91,7 +91,8 @@ def save_cache(c):
 
 
 def lookup(kernel, n):
-    """The cached best tuning for (kernel, size class), or None."""
+    """The cached best tuning for (kernel, size class), or None: nothing is
+    cached, or the library's default is the fastest."""
     e = load_cache().get(cache_key(kernel, n))
     return None if e is None else e["tune"]
 
@@ -166,10 +167,11 @@ def time_tunes(kernel, n, tunes, reps=20, warmup=3, device="cuda", sets=None):
 
 
 def tune(kernel, n, tunes=None, reps=20, save=True, device="cuda"):
-    """Times every candidate shape of ``kernel`` at ``n`` points; returns
+    """Times every candidate shape of ``kernel`` and the library's default (None)
+    at ``n`` points; returns
     {"tune": best, "us": time, "GB_s": algorithmic bandwidth, "table": [...]}."""
     if tunes is None:
-        tunes = list(candidates(ppts=PPTS + ((4,) if kernel in PPT4_KERNELS else ())))
+        tunes = list(candidates(ppts=PPTS + ((4,) if kernel in PPT4_KERNELS else ()))) + [None]
         if kernel == "christoffel":     # components of a point spread over lanes
             tunes += [{"block": b, "nt": True, "lanes": la}
                       for b in (64, 256) for la in (2, 3, 6, 9, 18)]
@@ -211,17 +213,26 @@ def plan_key(domains, kind="fwd"):
 
 
 def lookup_plan(domains, kind="fwd"):
-    """The cached best shape for subgrids like ``domains``, or None."""
+    """The cached best shape for subgrids like ``domains``, or None as for lookup."""
     e = load_cache().get(plan_key(domains, kind))
     return None if e is None else e["tune"]
 
 
+def plan_tune(domains, kind="fwd", want=None):
+    """The cached tuning of subgrids like ``domains`` (None: the library's
+    default), tuned now if nothing is cached."""
+    e = load_cache().get(plan_key(domains, kind))
+    return tune_plan(domains, kind=kind, want=want)["tune"] if e is None else e["tune"]
+
+
 def tune_plan(domains, tunes=None, reps=10, warmup=2, save=True, kind="fwd", want=None):
-    """Builds a plan of ``kind`` over ``domains`` for every candidate shape,
-    times its graph replay with HIP events (median of ``reps``) and returns
-    {"tune", "us", "table"} for the fastest; caches it under plan_key."""
+    """Builds a plan of ``kind`` over ``domains`` for every candidate shape and
+    for the library's default (None; over 256 subgrids of 8^3 to 48^3 points it
+    takes 559 us, the best shape 587), times its launch with HIP events (median
+    of ``reps``) and returns {"tune", "us", "table"} for the fastest; caches it
+    under plan_key."""
     from .ops import BatchPlan
-    tunes = list(plan_candidates()) if tunes is None else list(tunes)
+    tunes = list(plan_candidates()) + [None] if tunes is None else list(tunes)
     us = []
     for t in tunes:
         plan = BatchPlan(domains, tune=t, kind=kind, want=want)

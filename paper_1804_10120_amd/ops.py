@@ -571,9 +571,7 @@ class BatchPlan:
             if tune != "auto":
                 raise ValueError(f"tune={tune!r}: expected None, 'auto', a dict, a tuple or a Tune")
             from . import autotune
-            tune = autotune.lookup_plan(domains, kind=kind)
-            if tune is None:
-                tune = autotune.tune_plan(domains, kind=kind, want=want)["tune"]
+            tune = autotune.plan_tune(domains, kind=kind, want=want)
         want = (True,) * 6 if want is None else tuple(bool(x) for x in want)
         if len(want) != 6 or not any(want):
             raise ValueError("want: 6 booleans, at least one true")
