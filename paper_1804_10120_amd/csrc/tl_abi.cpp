@@ -220,22 +220,29 @@ tl::Resolved defaults(tl::KernelId k, int64_t n) {
 }
 
 // The kernel of a call that gives no launch shape (tl_stream.hpp), its tile
-// order and cache policies.  Figures: two or three buffer sets in turn, HIP
-// events, one run; "ragged": an output component that does not start on a line.
+// order and cache policies.  Figures: HIP events, one run; "warm": two or three
+// buffer sets in turn, "cold": so many that none is cached; "ragged": an output
+// component that does not start on a line.
 //
 // Staged (what it gains stands at Stage) from 2^20 points, where the adjoint
 // over 159^3 aligned points takes 483 us against 502 from registers, the forward
-// 267 / 278, and below 100^3 the two are within 2 %; if ragged from 2^16 points
-// (45^3 is a draw, at 61^3 the adjoint takes 26.2 / 29.7 us), and the same for
-// a batch, whose subgrids are ragged as a rule.  At exactly 2^20 and 2^21
-// aligned points the kernel with one tile range per XCD stays (Gamma over 128^3
-// 117 us against 120 staged in that order, the forward 134 / 135), unless
-// outputs are left out: only the default kernels skip the inputs of those.  Otherwise
-// one point per lane in blocks of 64, stored from registers, which at 33^3 to
-// 80^3 is the fastest or within 2 % of it; up to 2^16 points, one wave for each
-// SIMD of the chip, with a streaming body's inputs loaded first (one contraction
-// over 40^3 13.4 us against 14.8, over 52^3 34 / 29), if ragged up to 2^15 (the
-// three contractions over 31^3 10.8 / 10.6, over 37^3 18.8 / 16.2).
+// 267 / 278, and below 100^3 the two are within 2 %; if ragged from 3/2 2^16
+// points (cold, from registers / staged: the adjoint over 45^3 16.0 / 16.2 us,
+// over 47^3 18.2 / 16.0, over 57^3 33 / 25), for the streaming bodies of at least
+// 64 streams from 2^16 (one contraction over 41^3 warm 27 / 19 us, cold 27 / 25),
+// and the same for a batch, whose subgrids are ragged as a rule.
+// At exactly 2^20 and 2^21 aligned points the kernel with one tile range per XCD
+// stays (Gamma over 128^3 117 us against 120 staged in that order, the forward
+// 134 / 135), unless outputs are left out: only the default kernels skip the
+// inputs of those; and from 7/8 2^18 to 2^18 points, where the launch shape of a
+// few streams comes to one block for each compute unit, it stays for fewer than
+// 16 (the inverse over 63^3 points cold 5.6 us against 6.4, warm 5.2 / 5.4; over
+// 65^3 7.8 / 7.0).  Otherwise one point per lane in blocks of 64, stored from
+// registers, which at 33^3 to 80^3 is the fastest or within 2 % of it; up to
+// 2^16 points, one wave for each SIMD of the chip, with a streaming body's
+// inputs loaded first (one contraction over 40^3 13.4 us against 14.8, over 52^3
+// 34 / 29), if ragged up to 2^15 (the three contractions over 31^3 10.8 / 10.6,
+// over 37^3 18.8 / 16.2).
 // Two blocks per compute unit (24 KB of LDS reserved beside the kernel's 32)
 // only for bodies of at least 32 component streams: with 12 the few loads in
 // flight no longer cover their latency (the inverse over 159^3 82 us against
@@ -250,22 +257,34 @@ tl::Resolved defaults(tl::KernelId k, int64_t n) {
 // 8 and 16, Gamma 241, 240, 243 and 241 us); else plain order, which at 160^3
 // beats runs of 4 by 1-4 %.
 //
-// Cache policies.  The Infinity Cache (256 MiB) is worth using only for what
-// stays in it until its next use, so a call keeps at most a share of it:
-//  - inputs of at most 96 MiB are loaded through the caches: with three sets in
-//    turn the adjoint over 57^3 points takes 19.3 us against 23 streamed, the
-//    inverse over 100^3 14.8 / 17.7; with six sets, which do not fit, 4 % more;
-//  - outputs are left in the cache beside them only up to 32 MiB in all (at
-//    62 MB Gamma takes 10.3 us against 10.7 with three sets, 14.9 against 10.7
-//    with six);
-//  - with inputs beyond 96 MiB, outputs of less than 96 MiB are kept for the next
-//    kernel to find (Gamma over 84^3 points 34.0 us against 42.3 streamed, the
-//    covariant derivative over 100^3 49.3 / 52.1, d_t g over 97^3 26.7 / 29.4;
-//    with six sets within 2 %); staged ones only below 64 MiB (the forward over
-//    112^3 93 / 98, but over 127^3 ragged points 150 / 146), unless fewer than 64
-//    streams of less than 2^20 points are in flight (the gauge part of the adjoint
-//    over 97^3 points, 50 streams, 69 kept and 74.5 streamed, over 89^3 54 / 58,
-//    Gamma over 85^3 37 / 43; the whole adjoint, 83 streams, over 81^3 76 / 70).
+// Cache policies.  A streamed load finds what is in the Infinity Cache
+// (256 MiB) but leaves nothing there; a load through the caches pays when the
+// same input is read again soon and costs when it came from memory (the forward
+// over 32^3 points, 150 subgrids in turn: 4.97 us through the caches, 4.15
+// streamed).  So a call keeps what gains warm without losing cold against the
+// launch shape:
+//  - up to 2^16 points, and on ragged grids stored from registers, nothing (256
+//    forwards of 8^3 to 48^3 points replayed from a graph take 4.5 us each, 5.4
+//    with kept inputs, 5.4 with kept outputs);
+//  - larger aligned grids below 2^20: inputs of less than 32 MiB where a body of
+//    at least 20 streams writes about as much as it reads (Gamma over 48^3 warm
+//    6.7 us, 7.8 with kept outputs, 8.3 with neither; cold 9.0, 8.9, 8.7 and
+//    12.6 in the launch shape); else, from 3/4 2^18 points on, outputs of less
+//    than 96 MiB, for the next kernel to find (Gamma over 80^3 warm 28.3 / 32.2
+//    us, cold 33.8 / 32.8; the forward over 64^3 16.6 / 17.5 and 17.4 / 18.0);
+//  - the streaming bodies of at least 64 streams: inputs of less than 96 MiB
+//    (one contraction over 44^3 warm 18.0 / 25.3 us, cold 26.1 / 25.4);
+//  - staged ragged grids from 5/4 2^17 points: inputs of less than 96 MiB of
+//    at least 20 streams (Gamma over 57^3 warm 10.8 / 14.1 us, cold 15.5 / 14.8
+//    and 16.8 in the launch shape; over 49^3 cold 11.2 / 10.2 and 10.3);
+//  - staged grids with inputs beyond 96 MiB: outputs below 64 MiB (the forward
+//    over 112^3 93 / 98, but over 127^3 ragged points 150 / 146), or below 96 MiB
+//    when fewer than 64 streams of less than 2^20 points are in flight (the gauge
+//    part of the adjoint over 97^3 points, 50 streams, 69 kept and 74.5 streamed,
+//    over 89^3 54 / 58, Gamma over 85^3 37 / 43; the whole adjoint, 83 streams,
+//    over 81^3 76 / 70);
+//  - a batch, whose buffers a plan holds from run to run: inputs of less than
+//    96 MiB, and outputs beside them up to 32 MiB in all.
 // Ragged tiles share lines with their neighbours on the same XCD, and where a
 // body writes about as much as it reads and moves a lot, loads left in the L2
 // pay: the adjoint over 159^3 points 504 us against 534, the three contractions
@@ -275,14 +294,18 @@ void default_path(tl::KernelId k, const Layout& lay, int64_t n, tl::Resolved* r)
   const bool once = k == tl::KernelId::ChainBatchedOnce;
   const bool batched =
       k == tl::KernelId::ChainBatched || k == tl::KernelId::ChainBwdBatched || once;
-  const int64_t p16 = int64_t(1) << 16, p19 = int64_t(1) << 19, p20 = int64_t(1) << 20;
+  const int64_t p16 = int64_t(1) << 16, p18 = int64_t(1) << 18, p19 = int64_t(1) << 19,
+                p20 = int64_t(1) << 20;
   const int64_t in = lay.in_bytes >> 20, out = lay.out_bytes >> 20;  // MiB
+  const auto streams = [&](int64_t of) { return lay.in_bytes + lay.out_bytes >= of * 8 * n; };
   if (!lay.buf_ok || (batched && !once && n < p16)) return;
   const bool xcd = lay.line_ok && !batched && (n == p20 || n == 2 * p20);
   if (xcd && !lay.partial) return;
+  if (lay.line_ok && !batched && n > p18 - p18 / 8 && n <= p18 && !streams(16)) return;
+  const bool wide = k == tl::KernelId::Generic && streams(64);
   r->ppt = 1;
-  const auto streams = [&](int64_t of) { return lay.in_bytes + lay.out_bytes >= of * 8 * n; };
-  if (n >= p20 || once || (n >= p16 && (batched || !lay.line_ok))) {
+  if (n >= p20 || once || (batched && n >= p16) ||
+      (!lay.line_ok && n >= (wide ? p16 : p16 + p16 / 2))) {
     r->path = tl::Path::Staged;
     r->block = tl::kStageBlock;
     r->order = xcd ? tl::kOrderXcd : lay.line_ok ? 0 : 4;
@@ -291,9 +314,18 @@ void default_path(tl::KernelId k, const Layout& lay, int64_t n, tl::Resolved* r)
     r->block = tl::kSmallBlock;
     r->preload = n <= (lay.line_ok ? p16 : p16 / 2);
   }
-  r->keep_in = in < 96 || (!lay.line_ok && in >= 512 && 4 * out >= 3 * in);
-  const bool wide = r->path == tl::Path::Small || (n < p20 && !streams(64));
-  r->keep_out = in + out < 32 || (in >= 96 && out < (wide ? 96 : 64));
+  const bool even = 4 * out >= 3 * in;  // writes about as much as it reads
+  if (batched) {
+    r->keep_in = in < 96 || (!lay.line_ok && in >= 512 && even);
+    r->keep_out = in + out < 32 || (in >= 96 && out < 64);
+  } else if (r->path == tl::Path::Staged) {
+    r->keep_in = !lay.line_ok && ((in < 96 && (wide || (n >= 5 * p16 / 2 && streams(20)))) ||
+                                  (in >= 512 && even));
+    r->keep_out = (lay.line_ok || in >= 96) && out < (n < p20 && !streams(64) ? 96 : 64);
+  } else if (lay.line_ok && n > p16) {
+    r->keep_in = wide ? in < 96 : in < 32 && even && streams(20);
+    r->keep_out = !wide && !r->keep_in && n >= 3 * p16 && out < 96;
+  }
   if (r->path == tl::Path::Staged && n >= (lay.line_ok ? p20 : p19) && streams(32) &&
       !(n < p20 && r->keep_out && 4 * out >= in))
     r->lds_pad = 24 << 10;

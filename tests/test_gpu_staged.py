@@ -21,7 +21,8 @@ BWD = ("g", "dg", "beta", "K", "alpha", "w")
 # (n, leading-dimension padding or None for whole lines, offset of the field in its buffer)
 LAYOUTS = [(2 ** 16, 1, 0), (2 ** 16 + 1, 0, 3), (2 ** 16 + 255, 13, 15), (2 ** 16 + 256, 8, 0),
            (2 ** 19 - 1, 0, 0), (2 ** 19, None, 0), (2 ** 19 + 17, None, 0), (2 ** 19 + 241, 7, 1),
-           (2 ** 20, None, 0), (2 ** 20 + 1, None, 0), (2 ** 20 + 243, 1, 0)]
+           (2 ** 20, None, 0), (2 ** 20 + 1, None, 0), (2 ** 20 + 243, 1, 0),
+           (98303, 0, 0), (98304, 1, 3), (163840, 1, 0), (2 ** 18, None, 0), (2 ** 18 + 1, None, 0)]
 IDS = [f"n{n}pad{p}off{o}" for n, p, o in LAYOUTS]
 
 
