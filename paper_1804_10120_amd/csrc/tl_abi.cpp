@@ -239,10 +239,9 @@ tl::Resolved defaults(tl::KernelId k, int64_t n) {
 // 16 (the inverse over 63^3 points cold 5.6 us against 6.4, warm 5.2 / 5.4; over
 // 65^3 7.8 / 7.0).  Otherwise one point per lane in blocks of 64, stored from
 // registers, which at 33^3 to 80^3 is the fastest or within 2 % of it; up to
-// 2^16 points, one wave for each SIMD of the chip, with a streaming body's
-// inputs loaded first (one contraction over 40^3 13.4 us against 14.8, over 52^3
-// 34 / 29), if ragged up to 2^15 (the three contractions over 31^3 10.8 / 10.6,
-// over 37^3 18.8 / 16.2).
+// 3/2 2^16 points, at most two waves a SIMD, with a streaming body's inputs
+// loaded first (one contraction, cold, over 44^3 aligned points 23.7 us against
+// 27.0, over 48^3 30.8 / 30.1, over 39^3 ragged 20.1 / 25.9).
 // Two blocks per compute unit (24 KB of LDS reserved beside the kernel's 32)
 // only for bodies of at least 32 component streams: with 12 the few loads in
 // flight no longer cover their latency (the inverse over 159^3 82 us against
@@ -312,7 +311,7 @@ void default_path(tl::KernelId k, const Layout& lay, int64_t n, tl::Resolved* r)
   } else {
     r->path = tl::Path::Small;
     r->block = tl::kSmallBlock;
-    r->preload = n <= (lay.line_ok ? p16 : p16 / 2);
+    r->preload = n <= p16 + p16 / 2;
   }
   const bool even = 4 * out >= 3 * in;  // writes about as much as it reads
   if (batched) {

@@ -469,11 +469,11 @@ __device__ inline int64_t ordered_tile(int32_t order) {
 // points spread over the chip, stored from registers.
 // ALL: every input of a streaming body is loaded before its first store.  Loads
 // and stores retire in order, so where a body loads between its stores each
-// group waits for the stores before it, and with at most one wave per SIMD
-// nothing else runs meanwhile.  The registers that this takes (one contraction
-// 184 instead of 30) cost nothing there.  Without / with, three buffer sets in
-// turn: one contraction over 17^3 points 11.0 / 4.2 us, over 33^3 13.2 / 8.6;
-// two 6.3 / 4.5 and 10.6 / 9.0; three 5.1 / 4.6 and 10.4 / 9.5.
+// group waits for the stores before it, and with one or two waves per SIMD
+// little else runs meanwhile.  The registers that this takes (one contraction
+// 184 instead of 30) cost nothing there.  Without / with, buffers not cached:
+// one contraction over 17^3 points 15.4 / 3.9 us, over 33^3 21.6 / 10.5; two
+// 8.3 / 4.6 and 13.8 / 11.0; three 7.0 / 5.1 and 13.1 / 12.0.
 template <class Op, int LD, int ST, bool ALL>
 __global__ __launch_bounds__(kSmallBlock) void k_small(KArgs a, int64_t n) {
   const Bufs<Op> b = make_bufs<Op>(a, n);

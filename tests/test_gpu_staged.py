@@ -112,10 +112,12 @@ def test_expressions(name, lay):
 
 @pytest.mark.parametrize("name", ["mult3", "contract1", "contract2", "contract3"])
 @pytest.mark.parametrize("lay", [(1, 0, 0), (65, 0, 3), (2 ** 15, 1, 0), (2 ** 15 + 1, 0, 0), (2 ** 16, None, 0),
-                                 (2 ** 16 + 1, None, 0)],
-                         ids=["n1", "n65", "n32768pad1", "n32769", "n65536lines", "n65537lines"])
+                                 (2 ** 16 + 1, None, 0), (2 ** 16 - 1, 0, 0), (98304, None, 0),
+                                 (98305, None, 0)],
+                         ids=["n1", "n65", "n32768pad1", "n32769", "n65536lines", "n65537lines",
+                              "n65535", "n98304lines", "n98305lines"])
 def test_small_expressions(name, lay):
-    """Up to 2^16 points (2^15 if ragged) a streaming body loads all its inputs first."""
+    """Up to 3/2 2^16 points a streaming body loads all its inputs before its first store."""
     test_expressions(name, lay)
 
 
