@@ -230,7 +230,9 @@ tl::Resolved defaults(tl::KernelId k, int64_t n) {
 // points (cold, from registers / staged: the adjoint over 45^3 16.0 / 16.2 us,
 // over 47^3 18.2 / 16.0, over 57^3 33 / 25), for the streaming bodies of at least
 // 64 streams from 2^16 (one contraction over 41^3 warm 27 / 19 us, cold 27 / 25),
-// and the same for a batch, whose subgrids are ragged as a rule.
+// and for a batch, whose subgrids are ragged as a rule, from 2^18 points in all
+// (the forward over 144e3 points in 24 subgrids cold 12.6 / 12.7 us, the adjoint
+// over 156e3 22.4 / 24.4, the forward over 375e3 28.6 / 26.6).
 // At exactly 2^20 and 2^21 aligned points the kernel with one tile range per XCD
 // stays (Gamma over 128^3 117 us against 120 staged in that order, the forward
 // 134 / 135), unless outputs are left out: only the default kernels skip the
@@ -282,8 +284,8 @@ tl::Resolved defaults(tl::KernelId k, int64_t n) {
 //    part of the adjoint over 97^3 points, 50 streams, 69 kept and 74.5 streamed,
 //    over 89^3 54 / 58, Gamma over 85^3 37 / 43; the whole adjoint, 83 streams,
 //    over 81^3 76 / 70);
-//  - a batch, whose buffers a plan holds from run to run: inputs of less than
-//    96 MiB, and outputs beside them up to 32 MiB in all.
+//  - a batch: outputs below 64 MiB beside inputs beyond 96 MiB (the forward over
+//    746e3 points cold 48.1 / 49.4 us).
 // Ragged tiles share lines with their neighbours on the same XCD, and where a
 // body writes about as much as it reads and moves a lot, loads left in the L2
 // pay: the adjoint over 159^3 points 504 us against 534, the three contractions
@@ -297,13 +299,13 @@ void default_path(tl::KernelId k, const Layout& lay, int64_t n, tl::Resolved* r)
                 p20 = int64_t(1) << 20;
   const int64_t in = lay.in_bytes >> 20, out = lay.out_bytes >> 20;  // MiB
   const auto streams = [&](int64_t of) { return lay.in_bytes + lay.out_bytes >= of * 8 * n; };
-  if (!lay.buf_ok || (batched && !once && n < p16)) return;
+  if (!lay.buf_ok || (batched && !once && n < p18)) return;
   const bool xcd = lay.line_ok && !batched && (n == p20 || n == 2 * p20);
   if (xcd && !lay.partial) return;
   if (lay.line_ok && !batched && n > p18 - p18 / 8 && n <= p18 && !streams(16)) return;
   const bool wide = k == tl::KernelId::Generic && streams(64);
   r->ppt = 1;
-  if (n >= p20 || once || (batched && n >= p16) ||
+  if (n >= p20 || batched ||
       (!lay.line_ok && n >= (wide ? p16 : p16 + p16 / 2))) {
     r->path = tl::Path::Staged;
     r->block = tl::kStageBlock;
@@ -315,8 +317,8 @@ void default_path(tl::KernelId k, const Layout& lay, int64_t n, tl::Resolved* r)
   }
   const bool even = 4 * out >= 3 * in;  // writes about as much as it reads
   if (batched) {
-    r->keep_in = in < 96 || (!lay.line_ok && in >= 512 && even);
-    r->keep_out = in + out < 32 || (in >= 96 && out < 64);
+    r->keep_in = !lay.line_ok && in >= 512 && even;
+    r->keep_out = in >= 96 && out < 64;
   } else if (r->path == tl::Path::Staged) {
     r->keep_in = !lay.line_ok && ((in < 96 && (wide || (n >= 5 * p16 / 2 && streams(20)))) ||
                                   (in >= 512 && even));
