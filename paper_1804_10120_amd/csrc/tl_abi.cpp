@@ -236,10 +236,11 @@ tl::Resolved defaults(tl::KernelId k, int64_t n) {
 // At exactly 2^20 and 2^21 aligned points the kernel with one tile range per XCD
 // stays (Gamma over 128^3 117 us against 120 staged in that order, the forward
 // 134 / 135), unless outputs are left out: only the default kernels skip the
-// inputs of those; and from 7/8 2^18 to 2^18 points, where the launch shape of a
-// few streams comes to one block for each compute unit, it stays for fewer than
-// 16 (the inverse over 63^3 points cold 5.6 us against 6.4, warm 5.2 / 5.4; over
-// 65^3 7.8 / 7.0).  Otherwise one point per lane in blocks of 64, stored from
+// inputs of those; and from 7/8 2^18 to 2^18 points, where a launch shape of 512
+// threads and two points a lane comes to one block for each compute unit, it
+// stays for fewer than 16 streams (the inverse over 63^3 points cold 5.6 us
+// against 6.4, warm 5.2 / 5.4; over 65^3 7.8 / 7.0) and for the forward and
+// adjoint in one pass (63^3 36.2 / 38.2, 64^3 37.5 / 38.9).  Otherwise one point per lane in blocks of 64, stored from
 // registers, which at 33^3 to 80^3 is the fastest or within 2 % of it; up to
 // 3/2 2^16 points, at most two waves a SIMD, with a streaming body's inputs
 // loaded first (one contraction, cold, over 44^3 aligned points 23.7 us against
@@ -302,7 +303,9 @@ void default_path(tl::KernelId k, const Layout& lay, int64_t n, tl::Resolved* r)
   if (!lay.buf_ok || (batched && !once && n < p18)) return;
   const bool xcd = lay.line_ok && !batched && (n == p20 || n == 2 * p20);
   if (xcd && !lay.partial) return;
-  if (lay.line_ok && !batched && n > p18 - p18 / 8 && n <= p18 && !streams(16)) return;
+  if (lay.line_ok && !batched && n > p18 - p18 / 8 && n <= p18 &&
+      (!streams(16) || (k == tl::KernelId::ChainFwdBwd && !lay.partial)))
+    return;
   const bool wide = k == tl::KernelId::Generic && streams(64);
   r->ppt = 1;
   if (n >= p20 || batched ||
