@@ -184,11 +184,10 @@ typedef struct {
 typedef struct tl_batch_plan tl_batch_plan;
 
 /* Builds a plan that evaluates tl_dtg_chain on every domain with one kernel
- * launch over the tiles of all domains, also captured once into a HIP graph (by
- * default one block per tile; tune->grid_mult > 0 makes it persistent, each
- * block walking a contiguous chunk of tiles).  The plan copies the domain
- * table and its tile tables to device memory (its only device allocations,
- * freed by tl_batch_plan_destroy) and borrows the domains' buffers, which
+ * launch over the tiles of all domains (by default one block per tile;
+ * tune->grid_mult > 0 makes it persistent, each block walking a contiguous
+ * chunk of tiles).  The plan copies the domain table and its tile tables to
+ * device memory (its only device allocations, freed by tl_batch_plan_destroy) and borrows the domains' buffers, which
  * must outlive it; if any pointer changes, destroy the plan and create a new
  * one.  ndom >= 1; domains with n == 0 are allowed.  Validation is as for
  * tl_dtg_chain, per domain, plus: no domain's output may share an element
@@ -206,15 +205,15 @@ typedef struct {
 } tl_domain_bwd;
 
 /* The same for the adjoint: a plan that evaluates tl_dtg_chain_bwd on every
- * domain with one captured launch.  Ownership, validation and the functions
+ * domain with one launch.  Ownership, validation and the functions
  * below (launch, info, destroy) are as for tl_batch_plan_create. */
 tl_status tl_batch_plan_bwd_create(const tl_domain_bwd* doms, int32_t ndom, const tl_tune* tune,
                                    tl_batch_plan** out);
 
-/* Runs the plan's launch on `stream` (asynchronous): the kernel itself, or the
- * captured graph if the stream is being captured. */
+/* Runs the plan's launch on `stream` (asynchronous).  It is one kernel launch,
+ * so it may be captured into a HIP graph; the plan must outlive the graph. */
 tl_status tl_batch_plan_launch(tl_batch_plan* plan, void* stream);
-/* Launches the same kernel, never the graph (asynchronous). */
+/* The same launch (kept for callers of the graph-free entry point). */
 tl_status tl_batch_plan_launch_direct(tl_batch_plan* plan, void* stream);
 /* Total points, tiles and grid size of a plan (any pointer may be NULL). */
 tl_status tl_batch_plan_info(const tl_batch_plan* plan, int64_t* points, int64_t* tiles,

@@ -432,9 +432,6 @@ struct tl_batch_plan {
   tl::BatchDomain* d_doms = nullptr;
   int64_t* d_start = nullptr;
   int32_t* d_tile_dom = nullptr;
-  hipStream_t cap = nullptr;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
 };
 
 namespace tl {
@@ -901,7 +898,7 @@ tl_status plan_tables(tl::KernelId kid, PlanInput& in, const tl_tune* tune, Plan
   return TL_OK;
 }
 
-// Builds the tables, copies them to the device and captures the launch.
+// Builds the tables and copies them to the device.
 tl_status build_plan(tl::KernelId kid, PlanInput& in, const tl_tune* tune, tl_batch_plan** out) {
   PlanTables t;
   tl_status s = plan_tables(kid, in, tune, &t);
@@ -937,19 +934,6 @@ tl_status build_plan(tl::KernelId kid, PlanInput& in, const tl_tune* tune, tl_ba
     e = hipMemcpy(p->d_tile_dom, t.tile_dom.data(), sizeof(int32_t) * p->ntiles,
                   hipMemcpyHostToDevice);
     if (e != hipSuccess) return cleanup(e, "hipMemcpy(tile table)");
-  }
-  if (p->ntiles > 0) {
-    e = hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking);
-    if (e != hipSuccess) return cleanup(e, "hipStreamCreate");
-    e = hipStreamBeginCapture(p->cap, hipStreamCaptureModeThreadLocal);
-    if (e != hipSuccess) return cleanup(e, "hipStreamBeginCapture");
-    hipError_t le = tl::launch_batched(p->kid, p->r, p->d_doms, p->d_start, p->d_tile_dom,
-                                       p->ntiles, p->grid, p->chunk, p->cap);
-    e = hipStreamEndCapture(p->cap, &p->graph);
-    if (le != hipSuccess) return cleanup(le, "captured launch");
-    if (e != hipSuccess) return cleanup(e, "hipStreamEndCapture");
-    e = hipGraphInstantiate(&p->exec, p->graph, nullptr, nullptr, 0);
-    if (e != hipSuccess) return cleanup(e, "hipGraphInstantiate");
   }
   *out = p;
   return TL_OK;
@@ -1055,35 +1039,23 @@ static tl_status plan_device_check(const tl_batch_plan* p) {
   return TL_OK;
 }
 
-static tl_status plan_launch_kernel(const tl_batch_plan* p, hipStream_t s) {
-  hipError_t e = tl::launch_batched(p->kid, p->r, p->d_doms, p->d_start, p->d_tile_dom, p->ntiles,
-                                    p->grid, p->chunk, s);
-  if (e != hipSuccess) return hip_fail(e, "batched launch");
-  return TL_OK;
-}
-
-// The plan's graph holds one kernel node, and launching that kernel costs less
-// than replaying the graph: 6.2 us a call on the host against 18.3 (8 subgrids
-// of 8^3 to 12^3 points), 652 against 656 us over 256 subgrids.  The graph serves
-// a stream that is being captured.
+// A plan is one kernel launch and nothing else, so a stream that is being
+// captured takes it up as a kernel node.  (hipGraphLaunch on such a stream
+// succeeds and leaves the caller's graph without the work; outside a capture,
+// replaying a graph of this one node costs the host 18.3 us a call against 6.2,
+// for 8 subgrids of 8^3 to 12^3 points.)
 tl_status tl_batch_plan_launch(tl_batch_plan* p, void* stream) {
   if (p == nullptr) return fail(TL_ERR_NULL, "plan is NULL");
   if (plan_device_check(p) != TL_OK) return TL_ERR_INVALID;
   if (p->ntiles == 0) return TL_OK;
-  const hipStream_t s = static_cast<hipStream_t>(stream);
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone)
-    return plan_launch_kernel(p, s);
-  hipError_t e = hipGraphLaunch(p->exec, s);
-  if (e != hipSuccess) return hip_fail(e, "hipGraphLaunch");
+  hipError_t e = tl::launch_batched(p->kid, p->r, p->d_doms, p->d_start, p->d_tile_dom, p->ntiles,
+                                    p->grid, p->chunk, static_cast<hipStream_t>(stream));
+  if (e != hipSuccess) return hip_fail(e, "batched launch");
   return TL_OK;
 }
 
 tl_status tl_batch_plan_launch_direct(tl_batch_plan* p, void* stream) {
-  if (p == nullptr) return fail(TL_ERR_NULL, "plan is NULL");
-  if (plan_device_check(p) != TL_OK) return TL_ERR_INVALID;
-  if (p->ntiles == 0) return TL_OK;
-  return plan_launch_kernel(p, static_cast<hipStream_t>(stream));
+  return tl_batch_plan_launch(p, stream);
 }
 
 tl_status tl_batch_plan_info(const tl_batch_plan* p, int64_t* points, int64_t* tiles,
@@ -1107,10 +1079,7 @@ tl_status tl_batch_plan_destroy(tl_batch_plan* p) {
   keep(hipGetDevice(&prev));
   const bool switched = prev >= 0 && prev != p->device;
   if (switched) keep(hipSetDevice(p->device));
-  if (p->d_doms || p->d_start || p->d_tile_dom || p->exec) keep(hipDeviceSynchronize());
-  if (p->exec) keep(hipGraphExecDestroy(p->exec));
-  if (p->graph) keep(hipGraphDestroy(p->graph));
-  if (p->cap) keep(hipStreamDestroy(p->cap));
+  if (p->d_doms || p->d_start || p->d_tile_dom) keep(hipDeviceSynchronize());
   if (p->d_doms) keep(hipFree(p->d_doms));
   if (p->d_start) keep(hipFree(p->d_start));
   if (p->d_tile_dom) keep(hipFree(p->d_tile_dom));

@@ -547,7 +547,7 @@ def tl_batch_run_noalloc(domains, *, stream=None, tune=None):
 
 class BatchPlan:
     """tl_batch_plan_*: d_t g (kind="fwd") or its adjoint (kind="bwd") over
-    many subgrids in one launch (a graph node while a stream is captured).
+    many subgrids in one launch, which a HIP graph can capture.
 
     kind="fwd": ``domains`` is a sequence of dicts with the tensors g, dg,
     beta, dbeta, K, alpha and (optionally) dtg of one subgrid each.
@@ -631,7 +631,7 @@ class BatchPlan:
             check(lib().tl_batch_plan_launch(self._plan, _stream(self.device, stream)))
 
     def run_direct(self, stream=None):
-        """Launch the plan's kernel, never its graph."""
+        """The same launch."""
         with torch.cuda.device(self.device):
             check(lib().tl_batch_plan_launch_direct(self._plan, _stream(self.device, stream)))
 
