@@ -60,6 +60,7 @@ def call(name, *inputs, outs=None, stream=None, tune=None):
     """Runs generated program ``name``; returns the tuple of output fields.
     Output components that the program does not write are left untouched (so
     pass ``outs`` when they matter)."""
+    outs = None if outs is None else list(outs)
     if stream is None and tune is None and ops._recording() is None:
         r = _call_plain(name, inputs, outs)
         if r is not None:
@@ -70,7 +71,7 @@ def call(name, *inputs, outs=None, stream=None, tune=None):
     c = ops._Call()
     for t, spec in zip(inputs, p["inputs"]):
         c.add(t, spec["name"], spec["ncomp"])
-    outs = list(outs) if outs is not None else [None] * len(p["outputs"])
+    outs = [None] * len(p["outputs"]) if outs is None else outs
     if len(outs) != len(p["outputs"]):
         raise ValueError(f"{name}: expected outputs {[t['name'] for t in p['outputs']]}")
     outs = [c.out(o, spec["name"], inputs[0], spec["ncomp"]) for o, spec in zip(outs, p["outputs"])]

@@ -289,9 +289,14 @@ def tl_dtg_chain(g, dg, beta, dbeta, K, alpha, dtg=None, *, stream=None, tune=No
     return dtg
 
 
-def _mask(want, n):
-    """``want`` as bits, all set for None."""
-    return (1 << n) - 1 if want is None else sum(1 << k for k in range(n) if want[k])
+def _wanted(want, n):
+    """``want`` (any iterable) as a tuple of booleans, all set for None."""
+    return (True,) * n if want is None else tuple(bool(x) for x in want)
+
+
+def _mask(want):
+    """Booleans as bits."""
+    return sum(1 << k for k, x in enumerate(want) if x)
 
 
 GRAD_NAMES = ("g", "dg", "beta", "dbeta", "K", "alpha")
@@ -303,18 +308,18 @@ def tl_dtg_chain_bwd(g, dg, beta, K, alpha, w, g_bar=None, dg_bar=None, beta_bar
     """Adjoint of the fused chain for w = dL/d(d_t g) [6,n].
 
     Returns the tuple (g_bar, dg_bar, beta_bar, dbeta_bar, K_bar, alpha_bar).
-    ``want`` is a 6-tuple of booleans in that order; an unwanted gradient is
+    ``want`` holds 6 booleans in that order; an unwanted gradient is
     neither computed into memory nor allocated and comes back as None.
     """
-    if want is None or len(want) == 6:
-        r = _plain(_abi.CHAIN_BWD, _mask(want, 6), stream, tune, g, dg, beta, K, alpha, w,
+    want = _wanted(want, 6)
+    if len(want) == 6:
+        r = _plain(_abi.CHAIN_BWD, _mask(want), stream, tune, g, dg, beta, K, alpha, w,
                    g_bar, dg_bar, beta_bar, dbeta_bar, K_bar, alpha_bar)
         if r is not None:
             return r
     c = _Call()
     for t, name in ((g, "g"), (dg, "dg"), (beta, "beta"), (K, "K"), (alpha, "alpha"), (w, "w")):
         c.add(t, name)
-    want = (True,) * 6 if want is None else tuple(bool(x) for x in want)
     if len(want) != 6:
         raise ValueError("tl_dtg_chain_bwd: want has 6 entries")
     outs = [g_bar, dg_bar, beta_bar, dbeta_bar, K_bar, alpha_bar]
@@ -339,22 +344,23 @@ def tl_dtg_chain_fwd_bwd(g, dg, beta, dbeta, K, alpha, w, dtg=None, grads=None, 
 
     Returns (dtg, (g_bar, dg_bar, beta_bar, dbeta_bar, K_bar, alpha_bar)).
     ``grads`` optionally gives the six gradient outputs (None entries are
-    allocated when wanted); ``want`` is a 7-tuple of booleans for d_t g and the
+    allocated when wanted); ``want`` holds 7 booleans for d_t g and the
     six gradients; an unwanted output is not written and comes back as None.
     """
-    if (want is None or len(want) == 7) and (grads is None or len(grads) == 6):
-        r = _plain(_abi.CHAIN_FWD_BWD, _mask(want, 7), stream, tune, g, dg, beta, dbeta, K, alpha,
-                   w, dtg, *(grads if grads is not None else (None,) * 6))
+    want = _wanted(want, 7)
+    grads = [None] * 6 if grads is None else list(grads)
+    if len(want) == 7 and len(grads) == 6:
+        r = _plain(_abi.CHAIN_FWD_BWD, _mask(want), stream, tune, g, dg, beta, dbeta, K, alpha,
+                   w, dtg, *grads)
         if r is not None:
             return r[0], r[1:]
     c = _Call()
     for t, name in ((g, "g"), (dg, "dg"), (beta, "beta"), (dbeta, "dbeta"), (K, "K"),
                     (alpha, "alpha"), (w, "w")):
         c.add(t, name)
-    want = (True,) * 7 if want is None else tuple(bool(x) for x in want)
     if len(want) != 7:
         raise ValueError("tl_dtg_chain_fwd_bwd: want has 7 entries")
-    outs = [dtg] + (list(grads) if grads is not None else [None] * 6)
+    outs = [dtg] + grads
     if len(outs) != 7:
         raise ValueError("tl_dtg_chain_fwd_bwd: grads has 6 entries")
     ncomp = (6, 6, 18, 3, 9, 6, 1)
