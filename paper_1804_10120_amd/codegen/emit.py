@@ -232,10 +232,11 @@ class _Emitter:
 
     def _store_table(self, name, part) -> str:
         """constexpr function: the field (part 0) or component (part 1) of the k-th store."""
+        kind = "unsigned char" if max(st[part] for st in self.stores) <= 255 else "unsigned short"
         values = textwrap.fill(", ".join(str(st[part]) for st in self.stores), 92,
                                initial_indent="        ", subsequent_indent="        ")
         return (f"  static constexpr int {name}(int k) {{\n"
-                f"    constexpr unsigned char v[] = {{\n{values}}};\n"
+                f"    constexpr {kind} v[] = {{\n{values}}};\n"
                 f"    return v[k];\n  }}")
 
     def struct(self) -> str:

@@ -19,7 +19,9 @@ from ._abi import CField, Field, Tune, check, lib
 MANIFEST = os.path.join(os.path.dirname(os.path.abspath(__file__)), "generated.json")
 _programs = None
 _fns = {}
-_plain = {}     # name -> (address, component counts of inputs and outputs, and the input count)
+# name -> (address, component counts of inputs and outputs, and the input count, a byte each),
+# or None for a program with a field of more than 255 components
+_plain = {}
 
 
 def programs():
@@ -46,8 +48,11 @@ def _call_plain(name, inputs, outs):
     """The call made natively (csrc/py_bind.cpp), or None if it is not a plain one."""
     if name not in _plain:
         p = programs()[name]
-        comps = [t["ncomp"] for t in p["inputs"]], [t["ncomp"] for t in p["outputs"]]
-        _plain[name] = (_abi.address(_fn(name)), bytes((*comps[0], *comps[1], len(comps[0]))))
+        comps = [t["ncomp"] for t in p["inputs"] + p["outputs"]]
+        _plain[name] = None if max(comps) > 255 else (
+            _abi.address(_fn(name)), bytes((*comps, len(p["inputs"]))))
+    if _plain[name] is None:
+        return None
     address, comps = _plain[name]
     nout = len(comps) - 1 - comps[-1]
     outs = (None,) * nout if outs is None else outs
