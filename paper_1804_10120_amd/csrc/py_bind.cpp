@@ -349,6 +349,18 @@ PyObject* py_plan_launch(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
 
 // ---- The fused chain as an autograd node ------------------------------------
 
+// Whether the calls of this thread are being recorded (ops.record).  A backward
+// pass runs on the caller's thread where the engine's own are switched off, and
+// its call is then recorded as any other.
+thread_local bool t_recording = false;
+
+PyObject* py_recording(PyObject*, PyObject* on) {
+  const int v = PyObject_IsTrue(on);
+  if (v < 0) return nullptr;
+  t_recording = v != 0;
+  Py_RETURN_NONE;
+}
+
 // Takes the inputs of an entry, which it has checked once already.
 bool take_all(Entry e, const at::Tensor* const* t, Fields* f, tl_cfield* c) {
   for (int i = 0; i < kSpec[e].nin; ++i)
@@ -374,7 +386,7 @@ void check_native(tl_status st) {
 }
 
 // The adjoint through the Python entry point, for a saved tensor that a hook has
-// changed or a gradient that is not a plain tensor.
+// changed, a gradient that is not a plain tensor or a call that is recorded.
 torch::autograd::variable_list backward_python(const at::Tensor* const* in, const bool* wanted) {
   pybind11::gil_scoped_acquire gil;
   torch::autograd::variable_list grads(6);
@@ -445,7 +457,7 @@ struct DtgChain : torch::autograd::Function<DtgChain> {
       Fields f;
       tl_cfield c[6];
       tl_field o[6] = {};
-      if (watched() || !take_all(kBwd, in, &f, c) || !f.current()) {
+      if (t_recording || watched() || !take_all(kBwd, in, &f, c) || !f.current()) {
         grads = backward_python(in, wanted);
       } else {
         const bool flat = is_flat(saved[4]);
@@ -516,6 +528,7 @@ PyMethodDef kMethods[] = {
     {"noalloc", py_noalloc, METH_O, nullptr},
     {"plan_launch", TL_FAST(py_plan_launch), METH_FASTCALL, nullptr},
     {"dtg_chain", TL_FAST(py_dtg_chain), METH_FASTCALL, nullptr},
+    {"recording", py_recording, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_bind", nullptr, -1, kMethods,
                        nullptr, nullptr, nullptr, nullptr};

@@ -10,6 +10,7 @@ computation runs in the library's HIP kernels.
 from __future__ import annotations
 
 import ctypes
+import sys
 import threading
 
 import torch
@@ -177,11 +178,21 @@ class record:
         if _recording() is not None:
             raise RuntimeError("record() does not nest")
         _local.calls = []
+        self._tell(True)
         return _local.calls
 
     def __exit__(self, *exc):
         _local.calls = None
+        self._tell(False)
         return False
+
+    @staticmethod
+    def _tell(on):
+        """The extension's autograd node asks whether its thread is recording; a
+        node exists only once the extension is loaded."""
+        m = sys.modules.get(f"{__package__}._bind")
+        if m is not None:
+            m.recording(on)
 
 
 def _plain(entry, want, stream, tune, *fields):
