@@ -12,6 +12,7 @@ from __future__ import annotations
 
 import os
 import re
+import shutil
 import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
@@ -42,6 +43,17 @@ def _compile(src, verbose):
     return src, obj, r
 
 
+def _rocm_include():
+    """The HIP headers that belong to the compiler (HIPCC), else /opt/rocm's."""
+    found = shutil.which(HIPCC)
+    for root in ([os.path.dirname(os.path.dirname(p)) for p in (found, os.path.realpath(found))]
+                 if found else []):
+        inc = os.path.join(root, "include")
+        if os.path.exists(os.path.join(inc, "hip", "hip_runtime_api.h")):
+            return inc
+    return "/opt/rocm/include"
+
+
 def _compile_bind(verbose):
     """The torch binding's extension (csrc/py_bind.cpp): host code only."""
     import sysconfig
@@ -54,7 +66,7 @@ def _compile_bind(verbose):
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            "-isystem", os.path.join(t, "include"),
            "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
-           "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"],
+           "-isystem", _rocm_include(), "-isystem", sysconfig.get_paths()["include"],
            os.path.join(CSRC, "py_bind.cpp"), "-o", tmp, "-L", os.path.join(t, "lib"),
            "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
     if verbose:
