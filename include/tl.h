@@ -339,10 +339,11 @@ typedef struct {
  * "dtg_chain_batched", "dtg_chain_bwd_batched", or an expression name
  * "assign1" ... "contract3", "kij") would run with `tune` on a large grid
  * (ppt assumes aligned fields; a NULL tune is answered for the default members
- * given as a shape, the kernel that stores from registers).  VGPRs and scratch come from the HIP runtime,
- * SGPRs, AGPRs and the register-bound occupancy from the compiler's resource
- * report, compiled into the library when it was built, waves_per_simd from
- * the runtime's occupancy calculator; a value that cannot be obtained is -1.
+ * given as a shape, the kernel that stores from registers).  VGPRs and scratch
+ * come from the HIP runtime, SGPRs, AGPRs and the register-bound occupancy from
+ * the compiler's resource report, compiled into the library when it was built,
+ * waves_per_simd from the runtime's occupancy calculator; a value that cannot be
+ * obtained is -1.
  * Needs a HIP device (TL_ERR_HIP otherwise). */
 tl_status tl_kernel_info(const char* kernel, const tl_tune* tune, tl_kernel_attr* out);
 

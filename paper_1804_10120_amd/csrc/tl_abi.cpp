@@ -1110,9 +1110,12 @@ tl_status tl_kernel_info(const char* kernel, const tl_tune* tune, tl_kernel_attr
     if (std::strcmp(kExprName[e], kernel) == 0) expr = e;
   if (id == nullptr && expr < 0) return fail(TL_ERR_INVALID, "unknown kernel '%s'", kernel);
   tl::Resolved r;
-  tl_status s = resolve(id ? *id : tl::KernelId::Generic, tune, Layout{}, int64_t(1) << 24, &r);
+  // NULL stands for the default members given as a shape, not for the default
+  // kernel, whose launch is no shape.
+  const tl_tune members = {0, 0, TL_TUNE_NT, 0, 0};
+  tl_status s = resolve(id ? *id : tl::KernelId::Generic, tune != nullptr ? tune : &members,
+                        Layout{}, int64_t(1) << 24, &r);
   if (s != TL_OK) return s;
-  r.path = tl::Path::Shape;  // the kernel of the launch shape: it stores from registers
   const void* fn = id ? tl::kernel_address(*id, r) : tl::expr_address(expr, r);
   if (fn == nullptr) return fail(TL_ERR_INVALID, "no instantiation for this tuning");
   hipFuncAttributes attr;

@@ -507,7 +507,10 @@ def tl_expr(expr, *inputs, out=None, stream=None, tune=None):
 
 
 def tl_kernel_info(kernel, tune=None):
-    """Attributes (registers, scratch, ...) of the kernel a call would run."""
+    """Attributes (registers, scratch, ...) of the kernel a call with the launch
+    shape ``tune`` would run on a large grid; None: with the default members given
+    as a shape.  A call without a shape mostly runs another kernel, of the same
+    body, whose registers the compiler's report lists (_build/resource_usage.txt)."""
     a = KernelAttr()
     check(lib().tl_kernel_info(kernel.encode(), make_tune(tune), ctypes.byref(a)))
     return {k: getattr(a, k) for k, _ in KernelAttr._fields_}
