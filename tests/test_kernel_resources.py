@@ -21,3 +21,24 @@ def test_default_kernels_do_not_spill(kernel):
         assert scratch == 0, f"{name}: {scratch} bytes of scratch a lane"
         # two waves a SIMD: two blocks of 256 a compute unit, or eight of 64
         assert agprs == 0 and vgprs <= 256 and waves >= 2, f"{name}: {vgprs} + {agprs} registers"
+
+
+@pytest.mark.skipif(not os.path.exists(REPORT), reason="the library was not built here")
+def test_launch_shapes_keep_their_registers():
+    """The covariant derivative at two points a lane keeps four waves a SIMD in every block size,
+    and the adjoint at two points in blocks of 1024, which cannot but spill, stays at two cache lines
+    a lane with buffer addressing (a product rounded on its own for the three gradients it goes
+    into needed 188 bytes)."""
+    with open(REPORT) as f:
+        table = build.resource_table(f.read())
+
+    def rows(op, block, ppt, form=""):
+        want = f"k_pointsINS_{len(op)}{op}ELi{block}ELi{ppt}E{form}"
+        return [v for k, v in table.items() if want in k.replace("2tl", "")]
+    for block in (64, 128, 256, 512, 1024):
+        found = rows("OpCovDeriv", block, 2)
+        assert len(found) == 3
+        for sgprs, vgprs, agprs, scratch, waves in found:
+            assert waves >= 4 and scratch == 0, (block, vgprs, scratch, waves)
+    (buffered,) = rows("OpChainBwd", 1024, 2, "Lb1ELb1E")
+    assert buffered[3] <= 128, buffered
