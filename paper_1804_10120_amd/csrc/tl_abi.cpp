@@ -240,11 +240,19 @@ tl::Resolved defaults(tl::KernelId k, int64_t n) {
 // threads and two points a lane comes to one block for each compute unit, it
 // stays for fewer than 16 streams (the inverse over 63^3 points cold 5.6 us
 // against 6.4, warm 5.2 / 5.4; over 65^3 7.8 / 7.0) and for the forward and
-// adjoint in one pass (63^3 36.2 / 38.2, 64^3 37.5 / 38.9).  Otherwise one point per lane in blocks of 64, stored from
-// registers, which at 33^3 to 80^3 is the fastest or within 2 % of it; up to
+// adjoint in one pass (63^3 36.2 / 38.2, 64^3 37.5 / 38.9).
+// Otherwise one point per lane in blocks of 64, stored from registers; up to
 // 3/2 2^16 points, at most two waves a SIMD, with a streaming body's inputs
 // loaded first (one contraction, cold, over 44^3 aligned points 23.7 us against
-// 27.0, over 48^3 30.8 / 30.1, over 39^3 ragged 20.1 / 25.9).
+// 27.0, over 48^3 30.8 / 30.1, over 39^3 ragged 20.1 / 25.9).  A wide streaming
+// body that reads about one value for each that it stores keeps the launch shape
+// from 7/8 2^18 points, where loads first no longer pay and small blocks, each
+// waiting for its own stores between two loads, lose to blocks of 256 (one
+// contraction over aligned points, blocks of 64 / launch shape: 61^3 54.7 / 57.1
+// us, 62^3 63.4 / 60.8, 64^3 67.9 / 62.7, 72^3 97.7 / 92.3, 85^3 182 / 158, 96^3
+// 247 / 231; only 74^3 to 79^3 would gain, 3-14 %).  With nine or more loads in
+// flight at a time it does not (two contractions over 67^3 82.6 / 87.3, over 76^3
+// 119 / 146).
 // Two blocks per compute unit (24 KB of LDS reserved beside the kernel's 32)
 // only for bodies of at least 32 component streams: with 12 the few loads in
 // flight no longer cover their latency (the inverse over 159^3 82 us against
@@ -307,6 +315,9 @@ void default_path(tl::KernelId k, const Layout& lay, int64_t n, tl::Resolved* r)
       (!streams(16) || (k == tl::KernelId::ChainFwdBwd && !lay.partial)))
     return;
   const bool wide = k == tl::KernelId::Generic && streams(64);
+  const bool alternating = wide && lay.in_bytes >= lay.out_bytes &&
+                           8 * lay.in_bytes <= 9 * lay.out_bytes;
+  if (alternating && lay.line_ok && n > p18 - p18 / 8 && n < p20) return;
   r->ppt = 1;
   if (n >= p20 || batched ||
       (!lay.line_ok && n >= (wide ? p16 : p16 + p16 / 2))) {
