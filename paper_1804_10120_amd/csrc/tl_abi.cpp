@@ -236,11 +236,18 @@ tl::Resolved defaults(tl::KernelId k, int64_t n) {
 // At exactly 2^20 and 2^21 aligned points the kernel with one tile range per XCD
 // stays (Gamma over 128^3 117 us against 120 staged in that order, the forward
 // 134 / 135), unless outputs are left out: only the default kernels skip the
-// inputs of those; and from 7/8 2^18 to 2^18 points, where a launch shape of 512
-// threads and two points a lane comes to one block for each compute unit, it
-// stays for fewer than 16 streams (the inverse over 63^3 points cold 5.6 us
-// against 6.4, warm 5.2 / 5.4; over 65^3 7.8 / 7.0) and for the forward and
-// adjoint in one pass (63^3 36.2 / 38.2, 64^3 37.5 / 38.9).
+// inputs of those.  Below 2^20 points a launch shape of 512 threads with two
+// points a lane is at its best where its blocks just fill a turn of one block for
+// each compute unit (256: up to 2^18 points, then up to 2^19).  Aligned, it stays
+// in the last eighth of the first turn for fewer than 16 streams (the inverse
+// over 63^3 points cold 5.6 us against 6.4, warm 5.2 / 5.4; over 65^3 7.8 / 7.0)
+// and for the forward and adjoint in one pass (63^3 36.2 / 38.2, 64^3 37.5 /
+// 38.9).  Ragged, it needs every component on 16 bytes (a loose end of half a
+// line at most), and stays toward the end of either turn for the inverse, the
+// adjoint and the one-pass kernel (the inverse over 62^3 points, launch shape /
+// staged: 5.2 / 5.8 us, the adjoint 29.4 / 31.1, cold 31.3 / 35.3, in one pass
+// 34.3 / 36.8 and 36.5 / 42.7; over 78^3 the adjoint 64.6 / 69.0, in one pass
+// 74.7 / 81.0); the steps gain warm there what they lose cold and are staged.
 // Otherwise one point per lane in blocks of 64, stored from registers; up to
 // 3/2 2^16 points, at most two waves a SIMD, with a streaming body's inputs
 // loaded first (one contraction, cold, over 44^3 aligned points 23.7 us against
@@ -311,9 +318,17 @@ void default_path(tl::KernelId k, const Layout& lay, int64_t n, tl::Resolved* r)
   if (!lay.buf_ok || (batched && !once && n < p18)) return;
   const bool xcd = lay.line_ok && !batched && (n == p20 || n == 2 * p20);
   if (xcd && !lay.partial) return;
-  if (lay.line_ok && !batched && n > p18 - p18 / 8 && n <= p18 &&
-      (!streams(16) || (k == tl::KernelId::ChainFwdBwd && !lay.partial)))
-    return;
+  if (!batched && !lay.partial && lay.vec_ok && n >= p16) {
+    const int64_t blocks = (n + 1023) / 1024, cu = r->num_cu;
+    const auto fills = [&](int64_t turn, int64_t from) {  // from: in sixteenths
+      return 16 * blocks > (16 * (turn - 1) + from) * cu && blocks <= turn * cu;
+    };
+    const bool one_pass = k == tl::KernelId::ChainFwdBwd;
+    if (lay.line_ok && fills(1, 14) && (!streams(16) || one_pass)) return;
+    if (!lay.line_ok && (fills(1, 13) || fills(2, 10)) &&
+        (k == tl::KernelId::SymInverse || k == tl::KernelId::ChainBwd || one_pass))
+      return;
+  }
   const bool wide = k == tl::KernelId::Generic && streams(64);
   const bool alternating = wide && lay.in_bytes >= lay.out_bytes &&
                            8 * lay.in_bytes <= 9 * lay.out_bytes;
@@ -351,6 +366,7 @@ tl_status resolve(tl::KernelId k, const tl_tune* t, const Layout& lay, int64_t n
   tl::Resolved r = defaults(k, n);
   bool buf_ok = lay.buf_ok;
   if (t == nullptr) {
+    r.num_cu = num_cus();
     default_path(k, lay, n, &r);
   } else {
     const int l = t->lanes;

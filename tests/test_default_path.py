@@ -29,3 +29,26 @@ def test_alternating_bodies_keep_the_launch_shape(rule, comps):
 def test_other_wide_bodies_do_not(rule, comps):
     for n in (62 ** 3, 67 ** 3, 76 ** 3):
         assert rule("Generic", n, comps=comps)[0] == "small", n
+
+
+def test_last_blocks_of_a_turn(rule):
+    """Where blocks of 1024 points come to one or two for each compute unit, two points a lane: the
+    inverse, the adjoint and the one-pass kernel over ragged fields on 16 bytes, and on aligned ones
+    the kernels of few streams and the one-pass kernel."""
+    for cus in (256, 128):
+        one = cus * 1024
+        for kernel in ("SymInverse", "ChainBwd", "ChainFwdBwd"):
+            for n in (one * 13 // 16 + 8, one * 7 // 8 + 8, one - 8, one * 13 // 8 + 24,
+                      2 * one - 8):
+                assert rule(kernel, n, align=2, cus=cus)[0] == "shape", (kernel, n)
+                assert rule(kernel, n, align=1, cus=cus)[0] != "shape", (kernel, n)
+                if kernel != "SymInverse":      # left-out outputs: only read what is needed
+                    assert rule(kernel, n, align=2, partial=True, cus=cus)[0] != "shape"
+            for n in (one * 13 // 16 - 8, one + 8, one * 13 // 8 - 24, 2 * one + 8):
+                assert rule(kernel, n, align=2, cus=cus)[0] != "shape", (kernel, n)
+        for kernel in ("Christoffel", "CovDeriv", "Dtg", "Chain"):
+            assert rule(kernel, one - 8, align=2, cus=cus)[0] != "shape"
+        for kernel in ("SymInverse", "ChainFwdBwd"):
+            assert rule(kernel, one, cus=cus)[0] == "shape"
+            assert rule(kernel, one * 7 // 8, cus=cus)[0] == "small"
+        assert rule("ChainBwd", one, cus=cus)[0] == "small"
