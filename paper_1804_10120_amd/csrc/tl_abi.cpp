@@ -233,6 +233,15 @@ tl::Resolved defaults(tl::KernelId k, int64_t n) {
 // and for a batch, whose subgrids are ragged as a rule, from 2^18 points in all
 // (the forward over 144e3 points in 24 subgrids cold 12.6 / 12.7 us, the adjoint
 // over 156e3 22.4 / 24.4, the forward over 375e3 28.6 / 26.6).
+// Bodies of fewer than 20 streams have little to stage.  On ragged grids theirs
+// pays later, from 2^17 points (A_ij = B_ij, 18 streams, over 47^3 points cold,
+// from registers / staged 4.8 / 5.7 us, over 57^3 8.5 / 7.5), and where every
+// component starts on 16 bytes, so that a wave touches half as many broken lines,
+// from 2^20 as on aligned ones (over 50^3 5.4 / 6.0, mult1 over 58^3 5.9 / 6.5).
+// Below 12 streams a copy through LDS is never repaid and the launch shape stays
+// wherever the others are staged (A_i = B_i, 6 streams, launch shape / staged:
+// over 65^3 ragged points 4.3 / 5.0 us, over 111^3 14.0 / 14.9, over 144^3
+// aligned 24.8 / 28.5, over 159^3 32.9 / 37.5).
 // At exactly 2^20 and 2^21 aligned points the kernel with one tile range per XCD
 // stays (Gamma over 128^3 117 us against 120 staged in that order, the forward
 // 134 / 135), unless outputs are left out: only the default kernels skip the
@@ -333,9 +342,14 @@ void default_path(tl::KernelId k, const Layout& lay, int64_t n, tl::Resolved* r)
   const bool alternating = wide && lay.in_bytes >= lay.out_bytes &&
                            8 * lay.in_bytes <= 9 * lay.out_bytes;
   if (alternating && lay.line_ok && n > p18 - p18 / 8 && n < p20) return;
+  const int64_t ragged_from = wide               ? p16
+                              : streams(20)      ? p16 + p16 / 2
+                              : lay.vec_ok       ? p20
+                                                 : 2 * p16;
+  const bool staged = n >= p20 || batched || (!lay.line_ok && n >= ragged_from);
+  if (staged && !streams(12)) return;
   r->ppt = 1;
-  if (n >= p20 || batched ||
-      (!lay.line_ok && n >= (wide ? p16 : p16 + p16 / 2))) {
+  if (staged) {
     r->path = tl::Path::Staged;
     r->block = tl::kStageBlock;
     r->order = xcd ? tl::kOrderXcd : lay.line_ok ? 0 : 4;

@@ -52,3 +52,22 @@ def test_last_blocks_of_a_turn(rule):
             assert rule(kernel, one, cus=cus)[0] == "shape"
             assert rule(kernel, one * 7 // 8, cus=cus)[0] == "small"
         assert rule("ChainBwd", one, cus=cus)[0] == "small"
+
+
+def test_few_streams_are_staged_late(rule):
+    """Below 12 streams never, below 20 from 2^17 ragged points, or from 2^20 where every component
+    starts on 16 bytes."""
+    for comps in ((3, 3), (6, 3)):                      # assign1, add1
+        assert rule("Generic", 67 ** 3, align=2, comps=comps)[0] == "small", comps
+        for n, align in ((65 ** 3, 1), (111 ** 3, 1), (112 ** 3, 16), (159 ** 3, 16)):
+            assert rule("Generic", n, align=align, comps=comps)[0] == "shape", (comps, n)
+    for kernel, comps in (("SymInverse", None), ("Generic", (9, 9)), ("Generic", (10, 6))):
+        for n, align, path in ((47 ** 3, 1, "small"), (49 ** 3, 1, "small"), (51 ** 3, 1, "staged"),
+                               (50 ** 3, 2, "small"), (54 ** 3, 2, "small"), (66 ** 3, 2, "small"),
+                               (102 ** 3, 2, "staged"), (112 ** 3, 16, "staged")):
+            assert rule(kernel, n, align=align, comps=comps)[0] == path, (kernel, n, align)
+    for kernel in ("Christoffel", "CovDeriv", "Dtg", "ChainBwd", "ChainFwdBwd"):
+        for align in (1, 2):
+            assert rule(kernel, 47 ** 3, align=align)[0] == "staged"
+    # a batch is staged from 2^18 points in all, whatever its outputs
+    assert rule("ChainBwdBatched", P18, align=1, comps=(13, 1), partial=True)[0] == "staged"
