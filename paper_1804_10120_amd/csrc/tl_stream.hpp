@@ -465,6 +465,16 @@ __device__ inline int64_t ordered_tile(int32_t order) {
   return (run * 8 + (b & 7)) * order + (s - run * order);
 }
 
+// Streaming bodies whose inputs fit the registers all at once: three contractions
+// read 108 and come to 230 registers, two waves a SIMD and no scratch; one
+// contraction of a rank-4 tensor over four indices reads 272, which took every
+// register there is and 148 bytes of scratch a lane.
+constexpr int kPreloadMax = 112;
+template <class Op>
+constexpr bool preloads() {
+  return is_stream<Op>::value && Op::NIN <= kPreloadMax;
+}
+
 // Small grids: one point per lane in blocks of 64, so that even a few thousand
 // points spread over the chip, stored from registers.
 // ALL: every input of a streaming body is loaded before its first store.  Loads
@@ -657,9 +667,9 @@ static hipError_t launch_default_p(const Resolved& r, const KArgs& a, int64_t n,
   if (r.path == Path::Small) {
     const int64_t grid = (n + kSmallBlock - 1) / kSmallBlock;
     const dim3 blocks(static_cast<unsigned>(grid));
-    if (is_stream<Op>::value && r.preload)
-      hipLaunchKernelGGL((k_small<Op, LD, ST, is_stream<Op>::value>), blocks, dim3(kSmallBlock), 0,
-                         s, a, n);
+    if (preloads<Op>() && r.preload)
+      hipLaunchKernelGGL((k_small<Op, LD, ST, preloads<Op>()>), blocks, dim3(kSmallBlock), 0, s, a,
+                         n);
     else
       hipLaunchKernelGGL((k_small<Op, LD, ST, false>), blocks, dim3(kSmallBlock), 0, s, a, n);
   } else {

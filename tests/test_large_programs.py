@@ -1,13 +1,15 @@
 """Generated programs with fields of more than 255 components: the table of stores holds their
 component numbers, and the call goes through the Python marshalling."""
+import os
 import re
+import shutil
 import subprocess
 
 import pytest
 import torch
 
-from paper_1804_10120_amd import generated
-from paper_1804_10120_amd.codegen import Program, Tensor, indices
+from paper_1804_10120_amd import build, generated
+from paper_1804_10120_amd.codegen import Program, Sum, Tensor, indices
 from paper_1804_10120_amd.codegen.emit import _Emitter
 
 
@@ -39,3 +41,22 @@ def test_call_reaches_the_argument_checks(monkeypatch):
     monkeypatch.setattr(generated, "_fns", {"big": generated._fn("kij")})
     with pytest.raises(ValueError, match="expected a HIP device tensor"):
         generated.call("big", torch.zeros(256, 3, dtype=torch.float64))
+
+
+@pytest.mark.skipif(shutil.which(build.HIPCC) is None, reason="no compiler")
+def test_inputs_that_do_not_fit_registers_are_not_loaded_first(tmp_path):
+    """A contraction of a rank-4 tensor over four indices reads 272 components; the library's own
+    three contractions, 108, are loaded before the first store."""
+    a, b, c, d, m = indices("a b c d m", 4)
+    A, B, E = Tensor("A", (4,) * 4), Tensor("B", (4, 4)), Tensor("E", (4,) * 4)
+    p = Program("big", "a contraction").let(A[a, b, c, d], Sum(m, B[a, m] * E[m, b, c, d]))
+    src = tmp_path / "t.hip"
+    src.write_text("#include <hip/hip_runtime.h>\n"
+                   + "".join(f'#include "{os.path.join(build.CSRC, h)}"\n'
+                             for h in ("tl_internal.hpp", "tl_expr_ops.hpp", "tl_stream.hpp"))
+                   + "namespace tl {\n" + _Emitter(p).struct()
+                   + 'static_assert(Gen_big::NIN == 272 && !preloads<Gen_big>(), "");\n'
+                     'static_assert(preloads<OpContract<3>>() && !preloads<OpChain>(), "");\n}\n')
+    r = subprocess.run([build.HIPCC, *build.COMMON, "-fsyntax-only", str(src)],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[:800]
