@@ -359,19 +359,21 @@ void default_path(tl::KernelId k, const Layout& lay, int64_t n, tl::Resolved* r)
     r->preload = n <= p16 + p16 / 2;
   }
   const bool even = 4 * out >= 3 * in;  // writes about as much as it reads
+  bool inputs = false, outputs = false;
   if (batched) {
-    r->keep_in = !lay.line_ok && in >= 512 && even;
-    r->keep_out = in >= 96 && out < 64;
-  } else if (r->path == tl::Path::Staged) {
-    r->keep_in = !lay.line_ok && ((in < 96 && (wide || (n >= 5 * p16 / 2 && streams(20)))) ||
-                                  (in >= 512 && even));
-    r->keep_out = (lay.line_ok || in >= 96) && out < (n < p20 && !streams(64) ? 96 : 64);
+    inputs = !lay.line_ok && in >= 512 && even;
+    outputs = in >= 96 && out < 64;
+  } else if (staged) {
+    inputs = !lay.line_ok && ((in < 96 && (wide || (n >= 5 * p16 / 2 && streams(20)))) ||
+                              (in >= 512 && even));
+    outputs = (lay.line_ok || in >= 96) && out < (n < p20 && !streams(64) ? 96 : 64);
   } else if (lay.line_ok && n > p16) {
-    r->keep_in = wide ? in < 96 : in < 32 && even && streams(20);
-    r->keep_out = !wide && !r->keep_in && n >= 3 * p16 && out < 96;
+    inputs = wide ? in < 96 : in < 32 && even && streams(20);
+    outputs = !wide && n >= 3 * p16 && out < 96;
   }
-  if (r->path == tl::Path::Staged && n >= (lay.line_ok ? p20 : p19) && streams(32) &&
-      !(n < p20 && r->keep_out && 4 * out >= in))
+  r->keep = inputs ? tl::Keep::Inputs : outputs ? tl::Keep::Outputs : tl::Keep::Nothing;
+  if (staged && n >= (lay.line_ok ? p20 : p19) && streams(32) &&
+      !(n < p20 && r->keep == tl::Keep::Outputs && 4 * out >= in))
     r->lds_pad = 24 << 10;
 }
 

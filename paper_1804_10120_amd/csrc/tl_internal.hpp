@@ -44,6 +44,9 @@ constexpr int kSmallBlock = 64;  // block of k_small
 // Which kernel a call runs: the one of a launch shape, or one of the defaults.
 enum class Path { Shape, Small, Staged };
 
+// What a default kernel leaves in the caches.
+enum class Keep { Nothing, Inputs, Outputs };
+
 // A tuning request resolved to one compiled instantiation.
 struct Resolved {
   int block = 256;
@@ -55,11 +58,12 @@ struct Resolved {
   bool buf = false;  // buffer addressing (every field's extent below 4 GiB)
   int lanes = 1;     // lanes per grid point (tl_christoffel only)
   Path path = Path::Shape;
-  // of the default kernels: inputs and outputs left in the caches; of the
-  // staged one: the tile order (ordered_tile of tl_stream.hpp), and the LDS
-  // reserved beyond the kernel's own, which holds the blocks per compute unit
-  // down; of the small one: a streaming body loads all its inputs first
-  bool keep_in = false, keep_out = false, preload = false;
+  // of the default kernels: what stays in the caches; of the staged one: the
+  // tile order (ordered_tile of tl_stream.hpp), and the LDS reserved beyond the
+  // kernel's own, which holds the blocks per compute unit down; of the small
+  // one: a streaming body loads all its inputs first
+  Keep keep = Keep::Nothing;
+  bool preload = false;
   int32_t order = 0;
   uint32_t lds_pad = 0;
 };

@@ -77,7 +77,7 @@ struct ArgBatch {
 };
 static_assert(sizeof(ArgBatch) <= 4096, "kernel argument too large");
 
-template <int LD, int ST>
+template <int ST>
 __global__ __launch_bounds__(kStageBlock) void k_batched_args(ArgBatch batch) {
   __shared__ double buf[2][kStageComps][kStageBlock];
   const int64_t t = ordered_tile(batch.order);
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(kStageBlock) void k_batched_args(ArgBatch batch) {
   a.ldout[0] = w[19];
   const int64_t n = w[20];
   const Bufs<OpChain> b = make_bufs<OpChain>(a, n);
-  tile_staged<OpChain, LD, ST>(buf, a, b, n, (t - batch.start[d]) * kStageBlock);
+  tile_staged<OpChain, kCpolNT, ST>(buf, a, b, n, (t - batch.start[d]) * kStageBlock);
 }
 
 __global__ void k_copy(const double* __restrict__ src, double* __restrict__ dst, int64_t n) {
@@ -275,20 +275,25 @@ const void* kernel_address(KernelId k, const Resolved& r) {
   }
 }
 
-template <class Op>
-static const void* ptr_batched_staged(const Resolved& r) {
-#define TL_PTR(LD, ST) reinterpret_cast<const void*>(&k_batched_staged<Op, LD, ST>)
-  return TL_BY_POLICY(r, TL_PTR);
-#undef TL_PTR
+// The forward writes a seventh of what it reads and keeps no inputs (default_path).
+static const void* ptr_batched_staged(KernelId k, const Resolved& r) {
+#define TL_FWD(ST) reinterpret_cast<const void*>(&k_batched_staged<OpChain, kCpolNT, ST>)
+#define TL_BWD(LD, ST) reinterpret_cast<const void*>(&k_batched_staged<OpChainBwd, LD, ST>)
+  switch (k) {
+    case KernelId::ChainBatched:
+      return r.keep == Keep::Outputs ? TL_FWD(kCpolDev) : TL_FWD(kCpolNT);
+    case KernelId::ChainBwdBatched: return TL_BY_POLICY(r, TL_BWD);
+    default: return nullptr;
+  }
+#undef TL_FWD
+#undef TL_BWD
 }
 
 hipError_t launch_batched(KernelId k, const Resolved& r, const BatchDomain* doms, const int64_t* start,
                           const int32_t* tile_dom, int64_t ntiles, int64_t grid, int64_t chunk,
                           hipStream_t s) {
   if (r.path == Path::Staged) {
-    const void* fn = k == KernelId::ChainBatched      ? ptr_batched_staged<OpChain>(r)
-                     : k == KernelId::ChainBwdBatched ? ptr_batched_staged<OpChainBwd>(r)
-                                                      : nullptr;
+    const void* fn = ptr_batched_staged(k, r);
     if (fn == nullptr) return hipErrorInvalidValue;
     int32_t order = r.order;
     void* args[] = {const_cast<BatchDomain**>(&doms), const_cast<int64_t**>(&start),
@@ -310,9 +315,8 @@ hipError_t launch_batched(KernelId k, const Resolved& r, const BatchDomain* doms
 
 hipError_t launch_batched_args(const Resolved& r, const BatchDomain* doms, int32_t ndom,
                                hipStream_t s) {
-#define TL_PTR(LD, ST) reinterpret_cast<const void*>(&k_batched_args<LD, ST>)
-  const void* fn = TL_BY_POLICY(r, TL_PTR);
-#undef TL_PTR
+  const void* fn = r.keep == Keep::Outputs ? reinterpret_cast<const void*>(&k_batched_args<kCpolDev>)
+                                           : reinterpret_cast<const void*>(&k_batched_args<kCpolNT>);
   for (int32_t d0 = 0; d0 < ndom;) {
     ArgBatch batch;
     batch.order = r.order;

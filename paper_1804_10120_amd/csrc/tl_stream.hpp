@@ -658,18 +658,20 @@ __global__ __launch_bounds__(kStageBlock) void k_staged(KArgs a, int64_t n, int6
 }
 
 // LAUNCH(LD, ST) with the launch's cache policies.
-#define TL_BY_POLICY(r, LAUNCH)                                        \
-  ((r).keep_in ? ((r).keep_out ? LAUNCH(0, kCpolDev) : LAUNCH(0, kCpolNT)) \
-               : ((r).keep_out ? LAUNCH(kCpolNT, kCpolDev) : LAUNCH(kCpolNT, kCpolNT)))
+#define TL_BY_POLICY(r, LAUNCH)                            \
+  ((r).keep == Keep::Inputs    ? LAUNCH(0, kCpolNT)        \
+   : (r).keep == Keep::Outputs ? LAUNCH(kCpolNT, kCpolDev) \
+                               : LAUNCH(kCpolNT, kCpolNT))
 
 template <class Op, int LD, int ST>
 static hipError_t launch_default_p(const Resolved& r, const KArgs& a, int64_t n, hipStream_t s) {
   if (r.path == Path::Small) {
     const int64_t grid = (n + kSmallBlock - 1) / kSmallBlock;
     const dim3 blocks(static_cast<unsigned>(grid));
-    if (preloads<Op>() && r.preload)
-      hipLaunchKernelGGL((k_small<Op, LD, ST, preloads<Op>()>), blocks, dim3(kSmallBlock), 0, s, a,
-                         n);
+    // Grids small enough to be loaded first keep no outputs (default_path).
+    constexpr bool all = preloads<Op>() && ST == kCpolNT;
+    if (all && r.preload)
+      hipLaunchKernelGGL((k_small<Op, LD, ST, all>), blocks, dim3(kSmallBlock), 0, s, a, n);
     else
       hipLaunchKernelGGL((k_small<Op, LD, ST, false>), blocks, dim3(kSmallBlock), 0, s, a, n);
   } else {

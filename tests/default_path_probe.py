@@ -17,6 +17,7 @@ COMPS = {"SymInverse": (6, 6), "Christoffel": (24, 18), "CovDeriv": (30, 9), "Dt
          "Chain": (43, 6), "ChainBwd": (40, 43), "ChainFwdBwd": (49, 49),
          "ChainBatched": (43, 6), "ChainBwdBatched": (40, 43), "ChainBatchedOnce": (43, 6)}
 PATHS = ("shape", "small", "staged")
+KEEP = ("nothing", "inputs", "outputs")
 
 SOURCE = """
 #include "%s"
@@ -35,6 +36,7 @@ extern "C" void probe(int k, int64_t n, int align, int partial, int64_t in, int6
   res[0] = static_cast<int>(r.path);
   res[1] = r.block;
   res[2] = r.preload;
+  res[3] = static_cast<int>(r.keep);
 }
 """
 
@@ -44,13 +46,13 @@ class Rule:
         self.lib = lib
 
     def __call__(self, kernel, n, align=16, comps=None, partial=False, cus=256):
-        """(path, block, preload) of a call over n points; align: doubles that components are
-        aligned to."""
+        """(path, block, preload, kept) of a call over n points; align: doubles that components
+        are aligned to."""
         i, o = comps or COMPS[kernel]
-        res = (ctypes.c_int * 3)()
+        res = (ctypes.c_int * 4)()
         self.lib.probe(KERNELS.index(kernel), ctypes.c_int64(n), align, int(partial),
                        ctypes.c_int64(i), ctypes.c_int64(o), cus, res)
-        return PATHS[res[0]], res[1], bool(res[2])
+        return PATHS[res[0]], res[1], bool(res[2]), KEEP[res[3]]
 
 
 def load():

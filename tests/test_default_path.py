@@ -71,3 +71,33 @@ def test_few_streams_are_staged_late(rule):
             assert rule(kernel, 47 ** 3, align=align)[0] == "staged"
     # a batch is staged from 2^18 points in all, whatever its outputs
     assert rule("ChainBwdBatched", P18, align=1, comps=(13, 1), partial=True)[0] == "staged"
+
+
+def test_every_compiled_policy_is_reached(rule):
+    """What a kernel may keep in the caches is what it is compiled for: a grid that is loaded first
+    keeps no outputs, a forward batch no inputs; and every other combination occurs."""
+    seen = set()
+    bodies = [(k, None) for k in default_path_probe.COMPS]
+    bodies += [("Generic", c) for c in ((3, 3), (9, 9), (10, 6), (27, 27), (9, 27), (12, 81),
+                                        (90, 81), (99, 81), (108, 81))]
+    bodies += [("ChainBwdBatched", (40, 1)), ("ChainBwdBatched", (40, 21))]
+    sizes = [int(2 ** (9 + e / 8)) for e in range(0, 8 * 14)]
+    for kernel, comps in bodies:
+        for n in sizes:
+            for align in (1, 2, 16):
+                for m in (n, n // 16 * 16):
+                    path, _, preload, kept = rule(kernel, m, align=align, comps=comps,
+                                                  partial=comps in ((40, 1), (40, 21)))
+                    if path == "shape":
+                        assert kept == "nothing"
+                        continue
+                    group = kernel if "Batched" in kernel else path
+                    seen.add((group, preload and kernel == "Generic", kept))
+    loaded_first = {k for _, first, k in seen if first}
+    assert loaded_first == {"nothing", "inputs"}, loaded_first
+    for group, kept in (("small", {"nothing", "inputs", "outputs"}),
+                        ("staged", {"nothing", "inputs", "outputs"}),
+                        ("ChainBatched", {"nothing", "outputs"}),
+                        ("ChainBatchedOnce", {"nothing", "outputs"}),
+                        ("ChainBwdBatched", {"nothing", "inputs", "outputs"})):
+        assert {k for g, _, k in seen if g == group} == kept, group

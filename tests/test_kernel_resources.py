@@ -42,3 +42,17 @@ def test_launch_shapes_keep_their_registers():
             assert waves >= 4 and scratch == 0, (block, vgprs, scratch, waves)
     (buffered,) = rows("OpChainBwd", 1024, 2, "Lb1ELb1E")
     assert buffered[3] <= 128, buffered
+
+
+@pytest.mark.skipif(not os.path.exists(REPORT), reason="the library was not built here")
+def test_no_policy_is_compiled_that_no_call_reaches():
+    """Load policy 0 or 2 and store policy 16 or 2: inputs kept, outputs kept, neither, never both;
+    a grid that is loaded first keeps no outputs, a forward batch no inputs."""
+    with open(REPORT) as f:
+        table = build.resource_table(f.read())
+    both = [k for k in table if "ELi0ELi16E" in k]
+    assert not both, both[:3]
+    assert not [k for k in table if "k_small" in k and "ELi16ELb1E" in k]
+    assert sum("k_batched_args" in k for k in table) == 2
+    assert sum("16k_batched_stagedINS_7OpChainE" in k for k in table) == 2
+    assert sum("16k_batched_stagedINS_10OpChainBwdE" in k for k in table) == 3
