@@ -380,9 +380,9 @@ void default_path(tl::KernelId k, const Layout& lay, int64_t n, tl::Resolved* r)
 tl_status resolve(tl::KernelId k, const tl_tune* t, const Layout& lay, int64_t n,
                   tl::Resolved* out) {
   tl::Resolved r = defaults(k, n);
+  r.num_cu = num_cus();
   bool buf_ok = lay.buf_ok;
   if (t == nullptr) {
-    r.num_cu = num_cus();
     default_path(k, lay, n, &r);
   } else {
     const int l = t->lanes;
@@ -419,7 +419,6 @@ tl_status resolve(tl::KernelId k, const tl_tune* t, const Layout& lay, int64_t n
     r.ppt = 2;
   if (!lay.vec_ok) r.ppt = 1;
   r.buf = buf_ok;
-  r.num_cu = num_cus();
   *out = r;
   return TL_OK;
 }
