@@ -287,8 +287,12 @@ tl::Resolved defaults(tl::KernelId k, int64_t n) {
 // (256 MiB) but leaves nothing there; a load through the caches pays when the
 // same input is read again soon and costs when it came from memory (the forward
 // over 32^3 points, 150 subgrids in turn: 4.97 us through the caches, 4.15
-// streamed).  So a call keeps what gains warm without losing cold against the
-// launch shape:
+// streamed).  So a call keeps what gains warm and, but for two kinds of call, does
+// not lose cold against the launch shape.  The two: bodies of fewer than 16 streams
+// over 59^3 to 79^3 aligned points (outputs kept: A_i = B_i over 65^3 warm 2.9 us for
+// 4.0, cold 4.4 for 4.1; the inverse over 61^3 warm 4.8 / 5.1, cold 6.2 / 5.3), and
+// Gamma, nabla beta and d_t g over ragged points on 16 bytes just below 2^18 (inputs
+// kept: Gamma over 62^3 warm 13.9 / 17.7, cold 19.6 / 17.3).  Kept are:
 //  - up to 2^16 points, and on ragged grids stored from registers, nothing (256
 //    forwards of 8^3 to 48^3 points replayed from a graph take 4.5 us each, 5.4
 //    with kept inputs, 5.4 with kept outputs);

@@ -1,5 +1,7 @@
-// The batched forward chain with its tables in a fixed device array, for
-// callers that cannot allocate device memory (tl_batch_run_noalloc).
+// The batched forward chain with its tables in a fixed device array: what
+// tl_batch_run_noalloc, for callers that cannot allocate device memory, runs
+// when a launch shape is given or a field has 4 GiB or more.  (Otherwise the
+// descriptors travel in the kernel arguments, k_batched_args of tl_kernels.hip.)
 //
 // A batch plan keeps three tables in device memory it allocates: the domain
 // descriptors, the first tile of every domain, and the tile -> domain map.

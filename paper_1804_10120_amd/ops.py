@@ -526,13 +526,14 @@ def _fwd_domain(c, d):
 
 
 def tl_batch_run_noalloc(domains, *, stream=None, tune=None):
-    """tl_batch_run_noalloc: d_t g over many subgrids with the batched kernel,
-    its tables in the library's fixed device array (no device allocation).
+    """tl_batch_run_noalloc: d_t g over many subgrids with the batched kernel and
+    no device allocation: the subgrids are described in the kernel arguments.
 
     ``domains``: dicts with the tensors g, dg, beta, dbeta, K, alpha and dtg
-    (the output, which must be given: nothing is allocated here).  Calls that
-    overlap on one device race (they share the array); order them on one
-    stream.
+    (the output, which must be given: nothing is allocated here).  With a launch
+    shape, or a field of 4 GiB or more, the descriptions go to the library's
+    fixed device array instead: such calls race if they overlap on one device;
+    order them on one stream.
     """
     if stream is None and tune is None and _recording() is None:
         r = _abi.bind().noalloc(domains)

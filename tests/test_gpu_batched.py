@@ -1,5 +1,5 @@
-"""Many subgrids in one graph-captured persistent launch: every subgrid equals
-the plain fused kernel on that subgrid and the oracle."""
+"""Many subgrids in one launch: every subgrid equals the plain fused kernel on
+that subgrid and the oracle."""
 import numpy as np
 import pytest
 import torch
