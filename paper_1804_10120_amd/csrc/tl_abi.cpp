@@ -235,9 +235,9 @@ tl::Resolved defaults(tl::KernelId k, int64_t n) {
 // over 156e3 22.4 / 24.4, the forward over 375e3 28.6 / 26.6).
 // Bodies of fewer than 20 streams have little to stage.  On ragged grids theirs
 // pays later, from 2^17 points (A_ij = B_ij, 18 streams, over 47^3 points cold,
-// from registers / staged 4.8 / 5.7 us, over 57^3 8.5 / 7.5), and where every
+// from registers / staged 4.8 / 5.7 us, over 57^3 8.1 / 7.2), and where every
 // component starts on 16 bytes, so that a wave touches half as many broken lines,
-// from 2^20 as on aligned ones (over 50^3 5.4 / 6.0, mult1 over 58^3 5.9 / 6.5).
+// from 2^20 as on aligned ones (over 50^3 4.9 / 5.7, mult1 over 58^3 5.3 / 5.9).
 // Below 12 streams a copy through LDS is never repaid and the launch shape stays
 // wherever the others are staged (A_i = B_i, 6 streams, launch shape / staged:
 // over 65^3 ragged points 4.3 / 5.0 us, over 111^3 14.0 / 14.9, over 144^3
@@ -254,9 +254,9 @@ tl::Resolved defaults(tl::KernelId k, int64_t n) {
 // 38.9).  Ragged, it needs every component on 16 bytes (a loose end of half a
 // line at most), and stays toward the end of either turn for the inverse, the
 // adjoint and the one-pass kernel (the inverse over 62^3 points, launch shape /
-// staged: 5.2 / 5.8 us, the adjoint 29.4 / 31.1, cold 31.3 / 35.3, in one pass
-// 34.3 / 36.8 and 36.5 / 42.7; over 78^3 the adjoint 64.6 / 69.0, in one pass
-// 74.7 / 81.0); the steps gain warm there what they lose cold and are staged.
+// staged: 5.2 / 5.9 us, the adjoint 31.3 / 32.8, cold 32.2 / 36.2, in one pass
+// 35.9 / 38.2 and 37.0 / 42.8; over 78^3 the adjoint 63.6 / 68.0, in one pass
+// 74.2 / 78.5); the steps gain warm there what they lose cold and are staged.
 // Otherwise one point per lane in blocks of 64, stored from registers; up to
 // 3/2 2^16 points, at most two waves a SIMD, with a streaming body's inputs
 // loaded first (one contraction, cold, over 44^3 aligned points 23.7 us against
